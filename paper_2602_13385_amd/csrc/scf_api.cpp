@@ -308,6 +308,8 @@ void scf_plan_destroy(scf_plan* p) {
   if (p->d_beta_ang) (void)hipFree(p->d_beta_ang);
   if (p->d_kden) (void)hipFree(p->d_kden);
   if (p->d_dtab) (void)hipFree(p->d_dtab);
+  if (p->d_beta_img) (void)hipFree(p->d_beta_img);
+  if (p->d_rtab) (void)hipFree(p->d_rtab);
   if (p->d_cs) (void)hipFree(p->d_cs);
   if (p->d_fw) (void)hipFree(p->d_fw);
   delete p;
@@ -361,7 +363,7 @@ scf_status scf_forces(scf_plan* p, int64_t n, const void* x, const void* y, cons
   char* w = (char*)ws;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw, w + L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, w + L.W, s));
   }
   double cen[6] = {0, 0, 0, 0, 0, 0};
   if (with_host) {
@@ -378,12 +380,14 @@ scf_status scf_forces(scf_plan* p, int64_t n, const void* x, const void* y, cons
     HostParams<float> hp;
     fill_host_params(hp, with_host ? host : nullptr);
     return run_field<float>(p, n, (void*)x, (void*)y, (void*)z, nullptr, nullptr, nullptr, ax, ay,
-                            az, pot, w + L.W, hp, cen, 0, 0.0, 0.0, s);
+                            az, pot, w + L.W, hp, cen, 0, 0.0, 0.0, s, nullptr, nullptr, nullptr,
+                            nullptr, true);
   }
   HostParams<double> hp;
   fill_host_params(hp, with_host ? host : nullptr);
   return run_field<double>(p, n, (void*)x, (void*)y, (void*)z, nullptr, nullptr, nullptr, ax, ay, az,
-                           pot, w + L.W, hp, cen, 0, 0.0, 0.0, s);
+                           pot, w + L.W, hp, cen, 0, 0.0, 0.0, s, nullptr, nullptr, nullptr, nullptr,
+                           true);
 }
 
 }  // extern "C"
@@ -428,8 +432,9 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
   };
   double* coef_int = (double*)(w + L.coef);
   const size_t wrow = (size_t)(p->nmaxc + 1) * (p->lmax + 1) * (p->lmax + 1) * p->rs;
-  // force weights of the kick at x_k
-  auto Wk = [&](int k) -> void* { return w_hist ? (char*)w_hist + (size_t)k * wrow : w + L.W; };
+  void* FW = w + L.W;
+  // history row of the kick at x_k
+  auto Wk = [&](int k) -> void* { return w_hist ? (char*)w_hist + (size_t)k * wrow : nullptr; };
   const double h = 0.5 * dt;
   auto go = [&](auto tag) -> scf_status {
     using Rt = decltype(tag);
@@ -440,11 +445,10 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
     if (!(step_flags & SCF_STEP_ACC_VALID) || nsteps == 0) {
       // a(x0) from the particles themselves
       cen_row(row);
-      st = run_coeffs<Rt>(p, n, x, y, z, m, nsteps == 0 && coef_last ? coef_last : coef_int, Wk(0),
-                          w, L, s);
+      st = run_coeffs<Rt>(p, n, x, y, z, m, nsteps == 0 && coef_last ? coef_last : coef_int, FW,
+                          w, L, s, Wk(0));
       if (st != SCF_OK) return st;
-      st = run_field<Rt>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, Wk(0), hp, row, 0, 0.0,
-                         0.0, s);
+      st = run_field<Rt>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, FW, hp, row, 0, 0.0, 0.0, s);
       if (st != SCF_OK) return st;
     }
     if (nsteps == 0) return SCF_OK;
@@ -460,15 +464,15 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
     for (int k = 1; k <= nsteps; ++k) {
       const bool last = k == nsteps;
       cen_row(row);
-      st = run_coeffs<Rt>(p, n, x, y, z, m, last && coef_last ? coef_last : coef_int, Wk(k), w, L,
-                          s);
+      st = run_coeffs<Rt>(p, n, x, y, z, m, last && coef_last ? coef_last : coef_int, FW, w, L, s,
+                          Wk(k));
       if (st != SCF_OK) return st;
       // closing half kick of step k merged with the opening half kick of
       // step k+1, then the drift of step k+1
       // (the accelerations are stored on the last step only: the merged
       // kicks of the other steps do not read them back)
       st = run_field<Rt>(p, n, x, y, z, vx, vy, vz, last ? ax : nullptr, last ? ay : nullptr,
-                         last ? az : nullptr, nullptr, Wk(k), hp, row, 1, last ? h : dt,
+                         last ? az : nullptr, nullptr, FW, hp, row, 1, last ? h : dt,
                          last ? 0.0 : dt, s);
       if (st != SCF_OK) return st;
       centre_accel(hd, R, gc);
@@ -692,7 +696,7 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
   int max_cluster_rows = 0;
   for (int c = 0; c < ncl; ++c) max_cluster_rows = std::max(max_cluster_rows, rows[c + 1] - rows[c]);
   const bool one_pass = max_cluster_rows <= kSmallRows;
-  const int64_t W_stride = (int64_t)(p->nmaxc + 1) * (p->lmax + 1) * (p->lmax + 1);
+  const int64_t W_stride = (int64_t)fw_elems(p);
   double* coef_int = (double*)(w + B.L.coef);
   void* Wb = w + B.L.W;
 
@@ -729,6 +733,7 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     fa.az = (Rt*)az;
     fa.W = (const Rt*)Wb;
     fa.n = n;
+    fa.image = use_image(p, n / ncl);
     fa.host = hp;
     fa.blk_cluster = (const int32_t*)(w + B.blk_cluster);
     fa.blk_begin = (const int64_t*)(w + B.blk_begin);
@@ -746,19 +751,17 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
       }
       {
         Timed tr(p, q, K_REDUCE);
-        if (one_pass) {
-          HIP_TRY(launch_reduce_final_batched(
-              p->dtype, ca.partials, (const int32_t*)(w + B.rows), ncl, (int)p->T, p->nmax,
-              p->lmax, p->nmaxc, p->d_cs, p->d_fw, coef, Wb, W_stride,
-              (const double*)(w + B.tab), (double*)(w + B.cur), (int*)(w + B.ctr), q));
-        } else {
+        const void* part = ca.partials;
+        if (!one_pass) {
           HIP_TRY(launch_reduce_batched(p->dtype, ca.partials, (const int32_t*)(w + B.rows), ncl,
                                         (int)p->T, nch, (double*)(w + B.L.red1), q));
-          HIP_TRY(launch_finalize_batched(p->dtype, (const double*)(w + B.L.red1), nch, (int)p->T,
-                                          p->nmax, p->lmax, p->nmaxc, p->d_cs, p->d_fw, coef, Wb,
-                                          W_stride, (const double*)(w + B.tab), ncl,
-                                          (double*)(w + B.cur), (int*)(w + B.ctr), q));
+          part = w + B.L.red1;
         }
+        HIP_TRY(launch_reduce_final_batched(
+            p->dtype, !one_pass, part, (const int32_t*)(w + B.rows), nch,
+            one_pass ? max_cluster_rows : nch, ncl, weight_tables(p, use_image(p, n / ncl)), coef, Wb,
+            W_stride,
+            (const double*)(w + B.tab), (double*)(w + B.cur), (int*)(w + B.ctr), q));
       }
       ForceArgs<Rt> f2 = fa;
       f2.kick = Rt(kick);
@@ -944,11 +947,9 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
   };
   std::vector<double> S((size_t)(nsteps + 1) * 32, 0.0);
   auto Xk = [&](int k, int c) -> char* { return w + A.X + ((size_t)k * 3 + c) * n * rs; };
-  // force weights of the kick at X_k: recorded by the forward pass, or
-  // recomputed here into the workspace
-  auto Wk = [&](int k) -> char* {
-    return w_hist ? (char*)w_hist + (size_t)k * A.wsz * rs : w + A.Wsv + (size_t)k * A.wsz * rs;
-  };
+  // field weights of the kick at X_k: from the rows recorded by the forward
+  // pass, or recomputed here
+  auto Wk = [&](int k) -> char* { return w + A.Wsv + (size_t)k * A.wsz * rs; };
   char* Vb[3] = {w + A.V, w + A.V + n * rs, w + A.V + 2 * n * rs};
   char* Ab[3] = {w + A.A, w + A.A + n * rs, w + A.A + 2 * n * rs};
 
@@ -967,7 +968,11 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
         HIP_TRY(hipMemcpyAsync(Vb[c], src[3 + c], n * rs, hipMemcpyDeviceToDevice, s));
       }
       row_of(0, row);
-      if (!w_hist) {
+      if (w_hist) {
+        Timed t(p, s, K_MAKE_W);
+        HIP_TRY(launch_expand_w(p->dtype, w_hist, nsteps + 1,
+                                weight_tables(p, use_image(p, n)), w + A.Wsv, s));
+      } else {
         st = run_coeffs<Rt>(p, n, Xk(0, 0), Xk(0, 1), Xk(0, 2), m, (double*)(w + A.L.coef), Wk(0),
                             w, A.L, s);
         if (st != SCF_OK) return st;

@@ -247,15 +247,15 @@ scf_status density_impl(scf_plan* p, int64_t n, const void* x, const void* y, co
   void* W = ws + C.L.W;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw, W, s));
-    HIP_TRY(launch_scale_w(p->dtype, W, p->d_kden, p->lmax, p->nmaxc, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), p->d_kden, W, s));
   }
   HostParams<R> none;
   std::memset(&none, 0, sizeof(none));
   const size_t nr = (size_t)n * p->rs;
   char* acc = ws + C.acc;
   scf_status st = run_field<R>(p, n, (void*)x, (void*)y, (void*)z, nullptr, nullptr, nullptr, acc,
-                               acc + nr, acc + 2 * nr, rho, W, none, nullptr, 0, 0.0, 0.0, s);
+                               acc + nr, acc + 2 * nr, rho, W, none, nullptr, 0, 0.0, 0.0, s, nullptr,
+                               nullptr, nullptr, nullptr, true);
   if (st != SCF_OK) return st;
   Timed t(p, s, K_SELECT);
   HIP_TRY(launch_density_factor(p->dtype, n, x, y, z, 1.0 / p->basis.b, 1.0 / p->basis.alpha,
@@ -500,7 +500,7 @@ scf_status scf_step_frozen(scf_plan* p, int64_t n, void* x, void* y, void* z, vo
   fill_host_params(hd, with_host ? host : nullptr);
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw, w + L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, w + L.W, s));
   }
   double R[3] = {centre[0], centre[1], centre[2]}, V[3] = {centre[3], centre[4], centre[5]};
   const bool av = (step_flags & SCF_STEP_ACC_VALID) != 0;
@@ -534,8 +534,7 @@ scf_status scf_select(scf_plan* p, int64_t n, const void* x, const void* y, cons
   char* wsp = (char*)ws;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw,
-                          wsp + C.L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, wsp + C.L.W, s));
   }
   const size_t nr = (size_t)n * p->rs;
   char* acc = wsp + C.acc;
@@ -650,7 +649,7 @@ scf_status scf_evolve(scf_plan* p, int64_t n, void* x, void* y, void* z, void* v
   void* wnew = wsp + C.wnew;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw, W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, W, s));
   }
   auto go = [&](auto tag) -> scf_status {
     using Rt = decltype(tag);
@@ -739,7 +738,7 @@ scf_status scf_evolve(scf_plan* p, int64_t n, void* x, void* y, void* z, void* v
       if (n > 0) HIP_TRY(hipMemcpyAsync(w, wnew, nr, hipMemcpyDeviceToDevice, s));
       {
         Timed t(p, s, K_MAKE_W);
-        HIP_TRY(launch_make_w(p->dtype, coef, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_fw, W, s));
+        HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, W, s));
       }
       HIP_TRY(hipStreamSynchronize(s));
       state->nbound = sel.nbound;

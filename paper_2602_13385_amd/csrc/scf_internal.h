@@ -44,6 +44,52 @@ struct CoefArgs {
   int amode;
 };
 
+// Field weights of one coefficient vector, as the field kernels read them.
+// With W_n = fw_nlj a_nlj the force weights of row (l, j) (zero for n > nmax),
+// the potential of the row is G_l sum_n W_n p_n and, from x p_n = p_{n+1} +
+// beta_{n+1} p_{n-1} and (1 - x^2) p_n' = -n p_{n+1} + (n + 2 lam) beta_{n+1}
+// p_{n-1}, its radial derivative has the same prefactor:
+//   r d/dr [G_l sum_n W_n p_n] = G_l sum_k W^r_k p_k,  k = 0 .. nmaxc + 1,
+//   W^r_k = -1/2 [W_k + A_{k-1} W_{k-1} - A_{k+2} beta_{k+2} W_{k+1}],
+//   A_n = (2l+1) + n/alpha.
+// Degree 0, whose sum cancels as r -> 0, has the weights of d/dxi instead:
+// W'_k = 2 (k + lam) kappa_k sum_{n = k+1, k+3, ..} W_n / kappa_n.  The buffer is
+//   rows:  [(lmax+1)^2][nmaxc + 1]: W_0 .. W_nmaxc
+//   image: (single precision) the operand layout of the matrix-core kernel
+//          that reads it: degree l, quadruple q = m (nmaxc + 2) + k,
+//          (W^c, W^rc, W^s, W^rs)_k at registers q / 16, lanes 4 (q % 16) + 0..3
+// (The vector-ALU kernels read W alone and carry d p_n / d xi: with W^r in
+// their scalar loads too, the weights outgrow the scalar cache, 271 against
+// 219 us in double precision at 1e6 points, nmax 16, lmax 10.)
+struct FwLayout {
+  static __host__ __device__ constexpr int img0(int nmaxc, int lmax) {
+    return ((lmax + 1) * (lmax + 1) * (nmaxc + 1) + 63) / 64 * 64;
+  }
+  // operand registers of degree l, and of the degrees below l
+  static __host__ __device__ constexpr int nv(int l, int nmaxc) {
+    return ((l + 1) * (nmaxc + 2) + 15) / 16;
+  }
+  static __host__ __device__ constexpr int off(int l, int nmaxc) {
+    int s = 0;
+    for (int k = 0; k < l; ++k) s += nv(k, nmaxc);
+    return s;
+  }
+  // elements of the buffer (a multiple of 64)
+  static __host__ __device__ constexpr int elems(int nmaxc, int lmax, bool image) {
+    return img0(nmaxc, lmax) + (image ? 64 * off(lmax + 1, nmaxc) : 0);
+  }
+};
+// The device tables the weights are formed with (one set per plan).
+struct WeightTables {
+  int nmax, lmax, nmaxc;
+  int image;         // form the operand image too (single precision)
+  const double* cs;  // [T] sign and scale of the coefficients, n (lmax+1)^2 + (l, j)
+  const double* fw;  // [T] force weight per coefficient
+  // [lmax+1][2][nmaxc+2]: l >= 1, the factors of W_{k-1} and W_{k+1} in W^r_k;
+  // l = 0, 1 / kappa_k and 2 (k + lam) kappa_k
+  const double* rtab;
+};
+
 // Kernel arguments of the field (force / kick-drift) kernel.
 template <typename R>
 struct ForceArgs {
@@ -61,9 +107,11 @@ struct ForceArgs {
   R* az;
   R* pot;
   const R* mass;  // adjoint mode
-  const R* W;         // [(lmax+1)^2][(NMAXC+1)] force weights, n fastest
+  const R* W;         // field weights (FwLayout)
   const R* beta_rad;  // as in CoefArgs
   const R* beta_ang;
+  const R* beta_img;  // monic Gegenbauer recurrence to degree NMAXC + 1, [(lmax+1)][NMAXC+2]
+  int image;          // the matrix-core variants read the operand image (kImageRatio)
   int64_t n;
   R binv, alpha, inv_alpha;
   int amode;
@@ -76,7 +124,7 @@ struct ForceArgs {
   const int64_t* blk_begin;    // particle range of each block (batched mode)
   const int64_t* blk_end;
   const double* centre_tab;    // [nclusters][9]: R, grad psi_host(R), unused
-  int64_t W_stride;            // elements between clusters' W tables
+  int64_t W_stride;            // elements between clusters' field weights
   // matrix-core field pass: per degree, 1 / kappa_n and 2 (n + lam) kappa_n
   // (kappa_n the leading coefficient of C_n^lam), [l][2][NMAXC + 1]
   const double* dtab;
@@ -95,7 +143,7 @@ struct HvpArgs {
   T* lx;  // lambda_x (accumulated)
   T* ly;
   T* lz;
-  const T* W;  // force weights of the coefficients at x
+  const T* W;  // field weights of the coefficients at x
   const T* beta_rad;
   const T* beta_ang;
   int64_t n;
@@ -150,15 +198,20 @@ Engine* find_engine_f64_generic(int nmax, int lmax);
 // Small kernels independent of (nmax, lmax).
 hipError_t launch_reduce(int dtype, const void* partials, int nblocks, int T, int nchunks,
                          double* red1, hipStream_t s);
-hipError_t launch_finalize(int dtype, const double* red1, int nchunks, int T, int nmax, int lmax,
-                           int nmaxc, const double* cs, const double* fw, double* coef, void* W,
+// Sums of partial rows [0, nrows) (rows of T = (nmax+1)(lmax+1)^2 values, (l, j)
+// major, n fastest; real = the plan's type, or double chunk sums when
+// chunks_f64), then the coefficients (coef, nullable), the force weights of
+// one row of a weight history (W, nullable) and the field weights FW.
+hipError_t launch_reduce_final(int dtype, bool chunks_f64, const void* partials, int nrows,
+                               const WeightTables& wt, double* coef, void* W, void* FW,
+                               hipStream_t s);
+// field weights of a coefficient vector; kd (nullable, [l][nmaxc+1]) scales
+// the force weights first
+hipError_t launch_make_w(int dtype, const double* coef, const WeightTables& wt, const double* kd,
+                         void* FW, hipStream_t s);
+// field weights of `rows` force-weight rows of a history
+hipError_t launch_expand_w(int dtype, const void* W, int rows, const WeightTables& wt, void* FW,
                            hipStream_t s);
-// launch_reduce + launch_finalize in one pass, for few partial rows
-hipError_t launch_reduce_final_small(int dtype, const void* partials, int nblocks, int T, int nmax,
-                                    int lmax, int nmaxc, const double* cs, const double* fw,
-                                    double* coef, void* W, hipStream_t s);
-hipError_t launch_make_w(int dtype, const double* coef, int T, int nmax, int lmax, int nmaxc,
-                         const double* fw, void* W, hipStream_t s);
 hipError_t launch_kick_drift(int dtype, int64_t n, void* x, void* y, void* z, void* vx, void* vy,
                              void* vz, const void* ax, const void* ay, const void* az, double kick,
                              double drift, hipStream_t s);
@@ -166,17 +219,15 @@ hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t s);
 // batched mode (cluster-segmented) reduction and finalisation
 hipError_t launch_reduce_batched(int dtype, const void* partials, const int32_t* rows, int ncl,
                                  int T, int nchunks, double* red1, hipStream_t s);
-hipError_t launch_finalize_batched(int dtype, const double* red1, int nchunks, int T, int nmax,
-                                   int lmax, int nmaxc, const double* cs, const double* fw,
-                                   double* coef, void* W, int64_t W_stride,
-                                   const double* centre_tab, int ncl, double* cur, int* step,
-                                   hipStream_t s);
-// launch_reduce_batched + launch_finalize_batched in one pass, for few rows per cluster
-hipError_t launch_reduce_final_batched(int dtype, const void* partials, const int32_t* rows, int ncl,
-                                      int T, int nmax, int lmax, int nmaxc, const double* cs,
-                                      const double* fw, double* coef, void* W, int64_t W_stride,
-                                      const double* centre_tab, double* cur, int* step,
-                                      hipStream_t s);
+// cluster c's rows [rows[c], rows[c+1]) (chunks_f64: [c nchunks, (c+1) nchunks))
+// reduced and finalised as launch_reduce_final does; also copies row *step of
+// the centre table into cur and advances *step; max_rows: the most rows of a
+// cluster
+hipError_t launch_reduce_final_batched(int dtype, bool chunks_f64, const void* partials,
+                                      const int32_t* rows, int nchunks, int max_rows, int ncl,
+                                      const WeightTables& wt, double* coef, void* FW,
+                                      int64_t W_stride, const double* centre_tab, double* cur,
+                                      int* step, hipStream_t s);
 hipError_t launch_set_int(int* p, int v, hipStream_t s);
 // power per degree of ncl coefficient vectors (ncl x T in, ncl x (lmax+1) out)
 hipError_t launch_power(const double* coef, int nmax, int lmax, int ncl, double* El,
@@ -222,10 +273,8 @@ hipError_t launch_delta_compact(int dtype, int64_t n, const void* w0, const void
                                 int64_t* total, void* out, int64_t cap, hipStream_t s);
 // y += a x on n doubles
 hipError_t launch_axpy(int64_t n, double a, const double* x, double* y, hipStream_t s);
-// density (Eq. total_dens): force weights scaled by kd[l][n], then the radial
-// factor s^(1/alpha-2) (1 + s^(1/alpha))^-2 applied to the field pass's psi
-hipError_t launch_scale_w(int dtype, void* W, const double* kd, int lmax, int nmaxc,
-                          hipStream_t s);
+// density (Eq. total_dens): the radial factor s^(1/alpha-2) (1 + s^(1/alpha))^-2
+// applied to the field pass's psi
 hipError_t launch_density_factor(int dtype, int64_t n, const void* x, const void* y, const void* z,
                                  double binv, double inv_alpha, int amode, void* rho,
                                  hipStream_t s);

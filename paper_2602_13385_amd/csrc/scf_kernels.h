@@ -347,19 +347,19 @@ __global__ void __launch_bounds__(64 * WPB) coef_kernel(CoefArgs<R> a) {
     }
   }
   A* out = a.partials + ((int64_t)slot * ROWS + (LDS_COMBINE ? 0 : grp)) * a.T;
-  constexpr int AL2 = L1 * L1;
+  const int NC = a.nmax + 1;
 #pragma unroll
   for (int k = 0; k < KT; ++k) {
     if (tv[k] && (grp == 0 || !LDS_COMBINE)) {
       const int l = tl[k];
 #pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        if (i <= a.nmax) {
+      for (int j = 0; j < JT; ++j) {
+        const int jj = tj[k] + j;
+        if (jj <= 2 * l) {
+          A* o = out + (l * l + jj) * NC;
 #pragma unroll
-          for (int j = 0; j < JT; ++j) {
-            const int jj = tj[k] + j;
-            if (jj <= 2 * l) out[i * AL2 + l * l + jj] = acc[k][i][j];
-          }
+          for (int i = 0; i < NR; ++i)
+            if (i <= a.nmax) o[i] = acc[k][i][j];
         }
       }
     }
@@ -551,10 +551,29 @@ __device__ __forceinline__ void field_store(const ForceArgs<R>& a, const int64_t
                                             const R cx, const R cy, const R cz, const R gcx,
                                             const R gcy, const R gcz);
 
+// One load per 128-byte line of `bytes` bytes, spread over the block's 256
+// threads.  The field weights are written by the kernel before this one, so
+// every XCD's L2 misses them: fetched by the rows' own loads, a few at a time,
+// the misses line up one after another (in double precision at 1e5 points,
+// nmax 10, lmax 6, the pass took 16.6 us after a reduction and 11.7 us on warm
+// weights, with the lines requested first 12.3 us); issued together they cost
+// one latency, next to that of the positions.  touch_done() keeps the loads, at
+// the end of the kernel, after the stores: a volatile asm counts as a store,
+// and uniform loads after it would no longer be scalar.
+__device__ __forceinline__ uint32_t touch_lines(const void* p, const int bytes) {
+  uint32_t v = 0;
+  for (int o = threadIdx.x * 128; o < bytes; o += 256 * 128)
+    v |= *(const uint32_t*)((const char*)p + o);
+  return v;
+}
+__device__ __forceinline__ void touch_done(const uint32_t v) { asm volatile("" : : "v"(v)); }
+
 // Body of the field kernel: one particle per thread of a 256-thread block.
 template <typename R, int NMAXC, int LMAX, int MODE, bool BATCHED>
 __device__ __forceinline__ void field_body(const ForceArgs<R>& a) {
   int64_t i;
+  uint32_t tw;
+  constexpr int WB = (LMAX + 1) * (LMAX + 1) * (NMAXC + 1) * (int)sizeof(R);
   const R* __restrict__ W = a.W;
   R cx = a.cx, cy = a.cy, cz = a.cz, gcx = a.gcx, gcy = a.gcy, gcz = a.gcz;
   if constexpr (BATCHED) {
@@ -563,8 +582,9 @@ __device__ __forceinline__ void field_body(const ForceArgs<R>& a) {
     const int cl = __builtin_amdgcn_readfirstlane(a.blk_cluster[b]);
     const int64_t b0 = uniform_i64(a.blk_begin[b]), b1 = uniform_i64(a.blk_end[b]);
     i = b0 + threadIdx.x;
-    if (i >= b1) return;
     W = a.W + (int64_t)cl * a.W_stride;
+    tw = touch_lines(W, WB);
+    if (i >= b1) return;
     const double* ct = a.centre_tab + 9 * (int64_t)cl;
     cx = R(uniform_f64(ct[0]));
     cy = R(uniform_f64(ct[1]));
@@ -574,6 +594,7 @@ __device__ __forceinline__ void field_body(const ForceArgs<R>& a) {
     gcz = R(uniform_f64(ct[5]));
   } else {
     i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    tw = touch_lines(W, WB);
     if (i >= a.n) return;
   }
   const R x = a.x[i], y = a.y[i], z = a.z[i];
@@ -581,6 +602,7 @@ __device__ __forceinline__ void field_body(const ForceArgs<R>& a) {
   field_eval<R, NMAXC, LMAX>(x, y, z, W, a.beta_rad, a.beta_ang, a.binv, a.alpha, a.inv_alpha,
                              a.amode, psi, axv, ayv, azv);
   field_store<R, MODE>(a, i, x, y, z, psi, axv, ayv, azv, cx, cy, cz, gcx, gcy, gcz);
+  touch_done(tw);
 }
 
 // Field kernel body with each point's degrees split over S parts (for few
@@ -629,6 +651,8 @@ __device__ __forceinline__ void field_body_split(const ForceArgs<R>& a) {
   const int64_t i0 = (int64_t)blockIdx.x * P + t;
   const bool live = i0 < a.n;
   const int64_t i = live ? i0 : a.n - 1;  // every thread reaches the barrier
+  const uint32_t tw =
+      touch_lines(a.W, (LMAX + 1) * (LMAX + 1) * (NMAXC + 1) * (int)sizeof(R));
   const R x = a.x[i], y = a.y[i], z = a.z[i];
   const Geom<R> g = make_geom<R>(x, y, z, R(a.binv), R(a.alpha), R(a.inv_alpha), a.amode);
   int lo = sp.begin[0], hi = sp.begin[1] - 1;
@@ -663,6 +687,7 @@ __device__ __forceinline__ void field_body_split(const ForceArgs<R>& a) {
       field_store<R, MODE>(a, i, x, y, z, psi, axv, ayv, azv, a.cx, a.cy, a.cz, a.gcx, a.gcy,
                            a.gcz);
   }
+  touch_done(tw);
 }
 
 // Host tidal field and the stores of one particle: the forces (mode 0), the
@@ -1082,6 +1107,207 @@ template <int NMAXC, int LMAX, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
 field_mfma_kernel_o5(ForceArgs<float> a) {
   field_mfma_body<NMAXC, LMAX, MODE, true>(a);
+}
+
+// ---------------------------------------------------------------------------
+// field pass on the matrix cores from the operand image (single precision)
+// ---------------------------------------------------------------------------
+// The same sums with the radial derivative sigma^r = r d sigma / dr = G_l sum
+// W^r_k p_k in place of the xi-derivative (FwLayout), so that all four sums of
+// one (l, m) have the same factors: with the B operand G_l p_n and Q = Qt_l^m,
+//   P_m += Q sigma,  R_m += Q sigma^r,  Z_m += (dQ/dc) sigma
+// per order, and the azimuthal factors E_m = u^m are applied once at the end:
+//   psi = sum_m P_m . E_m,   r psi_r = sum_m R_m . E_m,   g_z = sum_m Z_m . E_m,
+//   (g_x, g_y) = sum_m m (P_m . E_{m-1}, P_m x E_{m-1}):
+// 6 fused multiply-adds per order and degree where field_eval_mfma takes 14.
+// Degree 0, whose r psi_r cancels as r -> 0, keeps the derivative form
+// psi_r = G_0' sigma / G_0 + (d xi / dr) G_0 sum W'_k p_k.  The operands are
+// read from the image that the reduction wrote in register layout: no LDS, no
+// barrier, no per-block build, every wave by itself; each XCD's L2 misses the
+// fresh image, so all its lines are requested first (touch_lines).  Measured
+// against the kernel above (us per step-mode launch after a reduction): 102
+// and 117 at 1e6 points, nmax 16, lmax 10; 7.4 and 10.2 at 1e5, nmax 10, lmax
+// 6; batched (against the vector kernel, which that path ran) see kImageRatio.
+// (The FP32 MFMAs run on the vector ALUs' own multipliers, here and in a
+// microbenchmark of separate waves, so the time is about the sum of the two.)
+
+// field_sums on the matrix cores at one point per lane; every lane of the wave
+// must be active (the MFMAs mix the lanes' operands).  img: the operand image
+// plus the lane.  Degrees and orders are compile-time sweeps, so one point's
+// whole evaluation is straight-line code that the scheduler can interleave.
+template <int NMAXC, int LMAX>
+__device__ __forceinline__ void field_sums_image(const Geom<float>& g,
+                                                const float* __restrict__ img,
+                                                const float* __restrict__ bF, float& psi,
+                                                float& psir, float& gx, float& gy, float& gz) {
+  constexpr int L1 = LMAX + 1, NP = NMAXC + 2;
+  float Gl = g.g0;
+  // Legendre factors: the ping-pong arrays of the VALU pass (degree l writes
+  // the array of its parity, reading the other one)
+  float QA[L1], QB[L1];
+  float PC[L1], PS[L1], RC[L1], RS[L1], ZC[L1], ZS[L1];
+  QA[0] = 1.f;
+  static_for<0, L1>([&](auto lc) {
+    constexpr int l = decltype(lc)::value;
+    float(&QW)[L1] = (l & 1) ? QB : QA;
+    const float(&QR)[L1] = (l & 1) ? QA : QB;
+    const float* __restrict__ src = img + FwLayout::off(l, NMAXC) * 64;
+    const float* __restrict__ b = bF + l * NP;
+    if constexpr (l > 0) Gl = Gl * g.w;
+    float p[NP];
+    p[0] = Gl;
+    p[1] = g.xi * Gl;
+#pragma unroll
+    for (int n = 2; n < NP; ++n) p[n] = g.xi * p[n - 1] - b[n] * p[n - 2];
+    float Qup = 0.f;
+    // orders from m = l down, in groups of up to MFMA_GROUP whose chains
+    // interleave (independent accumulators hide the matrix-core latency)
+    static_for_down<l, MFMA_GROUP>([&](auto mc) {
+      constexpr int mt = decltype(mc)::value;  // top order of the group
+      constexpr int gs = mt + 1 < MFMA_GROUP ? mt + 1 : MFMA_GROUP;
+      // the operand registers this group's quadruples lie in
+      constexpr int vlo = ((mt - gs + 1) * NP) >> 4, vhi = (mt * NP + NP - 1) >> 4;
+      float cw[vhi - vlo + 1];
+#pragma unroll
+      for (int v = vlo; v <= vhi; ++v) cw[v - vlo] = src[v * 64];
+      mfma_f4 acc[gs];
+      static_for<0, gs>([&](auto gc) {
+        constexpr int k = decltype(gc)::value;
+        acc[k] = mfma_f4{0.f, 0.f, 0.f, 0.f};
+      });
+      static_for<0, NP>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        static_for<0, gs>([&](auto gc) {
+          constexpr int k = decltype(gc)::value;
+          constexpr int q = (mt - k) * NP + n;
+          acc[k] = mfma_bcast<q>(cw[(q >> 4) - vlo], p[n], acc[k]);
+        });
+      });
+      static_for<0, gs>([&](auto gc) {
+        constexpr int k = decltype(gc)::value;
+        constexpr int m = mt - k;
+        // Qt_m^m = 1, Qt_{m+1}^m = c and dQt_m^m/dc = 0 are written out (a
+        // product with a zero or unit operand is not folded away under IEEE
+        // rules), and degree m starts order m's sums
+        float Q;
+        if constexpr (l == m)
+          Q = 1.f;
+        else if constexpr (l == m + 1)
+          Q = g.c;
+        else
+          Q = g.c * QR[m] - float(legendre_b(l, m)) * QW[m];
+        QW[m] = Q;
+        const float dQ = float(l - m) * Qup;
+        Qup = Q;
+        if constexpr (l == 0) {
+          psi = acc[k][0];
+          psir = g.dxi * acc[k][1] - g.kap * acc[k][0];
+          PC[0] = RC[0] = ZC[0] = 0.f;
+        } else if constexpr (l == m) {
+          PC[m] = acc[k][0];
+          RC[m] = acc[k][1];
+          PS[m] = acc[k][2];
+          RS[m] = acc[k][3];
+        } else {
+          PC[m] = fmaf(Q, acc[k][0], PC[m]);
+          RC[m] = fmaf(Q, acc[k][1], RC[m]);
+          if constexpr (m == 0) {
+            ZC[m] = fmaf(dQ, acc[k][0], ZC[m]);
+          } else {
+            PS[m] = fmaf(Q, acc[k][2], PS[m]);
+            RS[m] = fmaf(Q, acc[k][3], RS[m]);
+            if constexpr (l == m + 1) {
+              ZC[m] = dQ * acc[k][0];
+              ZS[m] = dQ * acc[k][2];
+            } else {
+              ZC[m] = fmaf(dQ, acc[k][0], ZC[m]);
+              ZS[m] = fmaf(dQ, acc[k][2], ZS[m]);
+            }
+          }
+        }
+        // the sums are due here: this keeps the compiler from holding every
+        // group's accumulators until the end of the sweep
+        asm("" : "+v"(PC[m]), "+v"(RC[m]));
+        if constexpr (m > 0) asm("" : "+v"(PS[m]), "+v"(RS[m]));
+        if constexpr (l > m) {
+          asm("" : "+v"(ZC[m]));
+          if constexpr (m > 0) asm("" : "+v"(ZS[m]));
+        }
+      });
+    });
+  });
+  psi += PC[0];
+  float rr = RC[0];
+  gx = 0.f;
+  gy = 0.f;
+  gz = ZC[0];
+  float er = 1.f, ei = 0.f;  // E_{m-1}
+  static_for<1, L1>([&](auto mc) {
+    constexpr int m = decltype(mc)::value;
+    const float c = float(m) * PC[m], s = float(m) * PS[m];
+    if constexpr (m == 1) {
+      gx = c;
+      gy = s;
+      er = g.ux;
+      ei = g.uy;
+    } else {
+      gx = fmaf(c, er, fmaf(s, ei, gx));
+      gy = fmaf(s, er, gy) - c * ei;
+      const float nr = er * g.ux - ei * g.uy;
+      ei = er * g.uy + ei * g.ux;
+      er = nr;
+    }
+    psi = fmaf(PC[m], er, fmaf(PS[m], ei, psi));
+    rr = fmaf(RC[m], er, fmaf(RS[m], ei, rr));
+    if constexpr (m < LMAX) gz = fmaf(ZC[m], er, fmaf(ZS[m], ei, gz));
+  });
+  psir = fmaf(g.ir, rr, psir);
+}
+
+// Body of the kernel: a wave evaluates 64 particles by itself; lanes past the
+// end evaluate the last particle (so that every lane joins the MFMAs) and store
+// nothing.  In batched mode every block lies inside one cluster, whose image it
+// reads.
+template <int NMAXC, int LMAX, int MODE, bool BATCHED>
+__device__ __forceinline__ void field_image_body(const ForceArgs<float>& a) {
+  int64_t i, end;
+  const float* __restrict__ W = a.W;
+  float cx = a.cx, cy = a.cy, cz = a.cz, gcx = a.gcx, gcy = a.gcy, gcz = a.gcz;
+  if constexpr (BATCHED) {
+    const int b = blockIdx.x;
+    const int cl = __builtin_amdgcn_readfirstlane(a.blk_cluster[b]);
+    i = uniform_i64(a.blk_begin[b]) + threadIdx.x;
+    end = uniform_i64(a.blk_end[b]);
+    W = a.W + (int64_t)cl * a.W_stride;
+    const double* ct = a.centre_tab + 9 * (int64_t)cl;
+    cx = float(uniform_f64(ct[0]));
+    cy = float(uniform_f64(ct[1]));
+    cz = float(uniform_f64(ct[2]));
+    gcx = float(uniform_f64(ct[3]));
+    gcy = float(uniform_f64(ct[4]));
+    gcz = float(uniform_f64(ct[5]));
+  } else {
+    i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    end = a.n;
+  }
+  const float* __restrict__ img = W + FwLayout::img0(NMAXC, LMAX);
+  const uint32_t tw = touch_lines(img, FwLayout::off(LMAX + 1, NMAXC) * 256);
+  const bool live = i < end;
+  const int64_t ic = live ? i : end - 1;
+  const float x = a.x[ic], y = a.y[ic], z = a.z[ic];
+  const Geom<float> g = make_geom<float>(x, y, z, a.binv, a.alpha, a.inv_alpha, a.amode);
+  float psi, psir, gx, gy, gz, axv, ayv, azv;
+  field_sums_image<NMAXC, LMAX>(g, img + (threadIdx.x & 63), a.beta_img, psi, psir, gx, gy, gz);
+  field_cartesian<float>(g, psir, gx, gy, gz, axv, ayv, azv);
+  if (live) field_store<float, MODE>(a, i, x, y, z, psi, axv, ayv, azv, cx, cy, cz, gcx, gcy, gcz);
+  touch_done(tw);
+}
+
+// (a budget of 4 waves per SIMD: 126 registers at nmax 16, lmax 10)
+template <int NMAXC, int LMAX, int MODE, bool BATCHED>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+field_image_kernel(ForceArgs<float> a) {
+  field_image_body<NMAXC, LMAX, MODE, BATCHED>(a);
 }
 
 // sum over the 64 lanes of a wave (every lane receives the total)
@@ -1587,8 +1813,10 @@ coef_blk_kernel(CoefArgs<R> a) {
         for (int n = 0; n < NR; ++n) store4(d + 4 * n, acc[n][0], acc[n][1], acc[n][2], acc[n][3]);
       }
       __syncthreads();
-      for (int t = tid; t < a.T; t += 256) {
-        const int n = t / L2, lj = t - n * L2;
+      for (int e = tid; e < L2 * NR; e += 256) {
+        const int lj = e / NR, n = e - lj * NR;
+        if (n > a.nmax) continue;
+        const int t = lj * (a.nmax + 1) + n;
         const int l = (int)sqrtf((float)lj + 0.5f), j = lj - l * l;
         // column of j in the l-block, and the tile holding it
         const int c = j == 0 ? 0 : j + 1;
@@ -1737,27 +1965,40 @@ struct EngineImpl final : Engine {
                           hipStream_t s) const override {
     if (nblocks <= 0) return hipSuccess;
     const ForceArgs<R>& fa = *(const ForceArgs<R>*)args;
+    const dim3 g((unsigned)nblocks);
+    if constexpr (sizeof(R) == 4) {
+      if ((fv == 2 || fv == 3) && fa.image) {
+        if (fa.blk_cluster)
+          field_image_kernel<NMAXC, LMAX, 1, true><<<g, 256, 0, s>>>(fa);
+        else if (mode == 0)
+          field_image_kernel<NMAXC, LMAX, 0, false><<<g, 256, 0, s>>>(fa);
+        else if (mode == 1)
+          field_image_kernel<NMAXC, LMAX, 1, false><<<g, 256, 0, s>>>(fa);
+        else
+          field_image_kernel<NMAXC, LMAX, 2, false><<<g, 256, 0, s>>>(fa);
+        return hipGetLastError();
+      }
+    }
     if constexpr (sizeof(R) == 4) {
       if ((fv == 2 || fv == 3) && mode != 2 && !fa.blk_cluster) {
         // nblocks tiles of 256 particles over at most one resident round of blocks
         static const int64_t cap[2] = {resident_blocks(field_mfma_kernel<NMAXC, LMAX, 1>),
                                        resident_blocks(field_mfma_kernel_o5<NMAXC, LMAX, 1>)};
-        const dim3 g((unsigned)(nblocks < cap[fv - 2] ? nblocks : cap[fv - 2]));
+        const dim3 gp((unsigned)(nblocks < cap[fv - 2] ? nblocks : cap[fv - 2]));
         if (fv == 2) {
           if (mode == 0)
-            field_mfma_kernel<NMAXC, LMAX, 0><<<g, 256, 0, s>>>(fa);
+            field_mfma_kernel<NMAXC, LMAX, 0><<<gp, 256, 0, s>>>(fa);
           else
-            field_mfma_kernel<NMAXC, LMAX, 1><<<g, 256, 0, s>>>(fa);
+            field_mfma_kernel<NMAXC, LMAX, 1><<<gp, 256, 0, s>>>(fa);
         } else {
           if (mode == 0)
-            field_mfma_kernel_o5<NMAXC, LMAX, 0><<<g, 256, 0, s>>>(fa);
+            field_mfma_kernel_o5<NMAXC, LMAX, 0><<<gp, 256, 0, s>>>(fa);
           else
-            field_mfma_kernel_o5<NMAXC, LMAX, 1><<<g, 256, 0, s>>>(fa);
+            field_mfma_kernel_o5<NMAXC, LMAX, 1><<<gp, 256, 0, s>>>(fa);
         }
         return hipGetLastError();
       }
     }
-    const dim3 g((unsigned)nblocks);
     if (fv >= kSplitVariant && !fa.blk_cluster) {
       // 128 (two parts) or 64 (four parts) particles a block
       const int64_t per = fv == kSplitVariant ? 128 : 64;

@@ -198,6 +198,8 @@ struct scf_plan {
   double* d_fw = nullptr;
   double* d_kden = nullptr;  // density constants -K_nl / (4 pi G b^2), [l][n]
   double* d_dtab = nullptr;  // radial derivative table of the matrix-core field pass, [l][2][n]
+  void* d_beta_img = nullptr;  // recurrence of the operand-image pass, [l][nmaxc + 2]
+  double* d_rtab = nullptr;    // radial-weight factors (WeightTables)
   std::vector<double> h_cs, h_fw;
   // kernel timing
   bool prof = false;
@@ -292,6 +294,25 @@ int coef_blocks_max(const scf_plan* p, int64_t n) {
 
 constexpr int kReduceChunks = 32;
 
+// elements of one coefficient vector's field weights
+size_t fw_elems(const scf_plan* p) {
+  return (size_t)FwLayout::elems(p->nmaxc, p->lmax, p->rs == 4);
+}
+// Whether the matrix-core variants read the operand image (the faster kernel
+// at every size) in a run of clusters of n particles.  The two kernels sum in
+// different orders, and a run amplifies the last bits of its forces: after ten
+// steps of 0.01 the coefficients differ by about 1e-8 sqrt(T / n) (measured 4 to
+// 14e-10 at n = 130 T over five basis sizes, Plummer and Hernquist).  Clusters
+// of fewer than kImageRatio T particles keep the kernels, and the bits, that
+// their runs have had.  Single evaluations (scf_forces, the density) amplify
+// nothing and use the image at every n.
+constexpr int64_t kImageRatio = 160;
+bool use_image(const scf_plan* p, int64_t n) { return n >= kImageRatio * p->T; }
+WeightTables weight_tables(const scf_plan* p, bool image) {
+  return WeightTables{p->nmax, p->lmax, p->nmaxc, image && p->rs == 4, p->d_cs, p->d_fw,
+                      p->d_rtab};
+}
+
 struct WsLayout {
   size_t partials, red1, coef, W, total;
 };
@@ -307,8 +328,7 @@ WsLayout ws_layout(const scf_plan* p, int64_t n, int nclusters, int nblocks) {
   L.coef = off;
   off += align256((size_t)p->T * sizeof(double) * std::max(nclusters, 1));
   L.W = off;
-  off += align256((size_t)(p->nmaxc + 1) * (p->lmax + 1) * (p->lmax + 1) * p->rs *
-                  std::max(nclusters, 1));
+  off += align256(fw_elems(p) * p->rs * std::max(nclusters, 1));
   L.total = off;
   (void)n;
   return L;
@@ -413,6 +433,7 @@ void fill_force_common(ForceArgs<R>& fa, const scf_plan* p) {
   fa.inv_alpha = R(1.0 / p->basis.alpha);
   fa.amode = p->amode;
   fa.dtab = p->d_dtab;
+  fa.beta_img = (const R*)p->d_beta_img;
 }
 
 template <typename R>
@@ -430,17 +451,18 @@ void fill_coef_common(CoefArgs<R>& ca, const scf_plan* p) {
 }
 
 // Sum of `rows` partial rows (FP32 or FP64) in double precision, then the
-// coefficients (coef, nullable) and force weights W.  Up to kSmallRows rows:
-// one pass (16 coefficients per block of 1024 threads, 64 row groups);
-// otherwise chunk sums then their sum (two launches, fixed order either way).
+// coefficients (coef, nullable), the force weights of a history row (W,
+// nullable) and the field weights FW (with the operand image: image).  Up to kSmallRows rows: one pass (a
+// block of 1024 threads per (l, j)); otherwise chunk sums first (two launches,
+// fixed order either way).
 constexpr int kSmallRows = 2048;
 
 scf_status reduce_and_finalize(scf_plan* p, const void* partials, int rows, double* coef, void* W,
-                               char* ws, const WsLayout& L, hipStream_t s) {
+                               void* FW, bool image, char* ws, const WsLayout& L, hipStream_t s) {
+  const WeightTables wt = weight_tables(p, image);
   if (rows <= kSmallRows) {
     Timed t(p, s, K_REDUCE);
-    HIP_TRY(launch_reduce_final_small(p->dtype, partials, rows, (int)p->T, p->nmax, p->lmax,
-                                      p->nmaxc, p->d_cs, p->d_fw, coef, W, s));
+    HIP_TRY(launch_reduce_final(p->dtype, false, partials, rows, wt, coef, W, FW, s));
     return SCF_OK;
   }
   double* red1 = (double*)(ws + L.red1);
@@ -451,29 +473,31 @@ scf_status reduce_and_finalize(scf_plan* p, const void* partials, int rows, doub
   }
   {
     Timed t(p, s, K_FINALIZE);
-    HIP_TRY(launch_finalize(p->dtype, red1, nch, (int)p->T, p->nmax, p->lmax, p->nmaxc, p->d_cs,
-                            p->d_fw, coef, W, s));
+    HIP_TRY(launch_reduce_final(p->dtype, true, red1, nch, wt, coef, W, FW, s));
   }
   return SCF_OK;
 }
 
-// coefficients of n particles into coef (device) and force weights W (device)
+// coefficients of n particles into coef (device, nullable) and field weights FW
+// (device); with W non-null also the force weights of a history row
 template <typename R>
 scf_status run_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, const void* z,
-                      const void* m, double* coef, void* W, char* ws, const WsLayout& L, hipStream_t s) {
+                      const void* m, double* coef, void* FW, char* ws, const WsLayout& L,
+                      hipStream_t s, void* W = nullptr) {
   int64_t stages;
   const int units = coef_units(p, n, &stages);
   const int rpu = units > 0 ? unit_rows(p, p->coef_variant, (stages + units - 1) / units) : 1;
   const int nb = units * rpu;
   if (n == 0) {
     // empty particle set: all coefficients vanish
+    // (every caller with n = 0 passes coef and no history row)
     if (coef) {
       Timed t(p, s, K_FILL);
       HIP_TRY(launch_fill(coef, p->T, 0.0, s));
     }
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef ? coef : (double*)(ws + L.coef), (int)p->T, p->nmax,
-                          p->lmax, p->nmaxc, p->d_fw, W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef ? coef : (double*)(ws + L.coef), weight_tables(p, true), nullptr,
+                          FW, s));
     return SCF_OK;
   }
   CoefArgs<R> ca;
@@ -492,18 +516,19 @@ scf_status run_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, cons
     Timed t(p, s, K_COEF);
     HIP_TRY(p->eng->launch_coef(&ca, units, p->coef_variant, s));
   }
-  return reduce_and_finalize(p, ca.partials, nb, coef, W, ws, L, s);
+  return reduce_and_finalize(p, ca.partials, nb, coef, W, FW, use_image(p, n), ws, L, s);
 }
 
 // Field pass over n particles.  mode 0: a (and psi) into ax, ay, az (pot);
 // mode 1: kick by `kick`, drift by `drift` with the drifted positions written
 // to xo (default: in place); mode 2: adjoint accumulation (see field_kernel).
+// single: an evaluation that no run continues from (use_image).
 template <typename R>
 scf_status run_field(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx, void* vy,
                      void* vz, void* ax, void* ay, void* az, void* pot, const void* W,
                      const HostParams<R>& hp, const double* cen, int mode, double kick,
                      double drift, hipStream_t s, void* xo = nullptr, void* yo = nullptr,
-                     void* zo = nullptr, const void* mass = nullptr) {
+                     void* zo = nullptr, const void* mass = nullptr, bool single = false) {
   if (n == 0) return SCF_OK;
   ForceArgs<R> fa;
   fill_force_common(fa, p);
@@ -523,6 +548,7 @@ scf_status run_field(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
   fa.pot = (R*)pot;
   fa.W = (const R*)W;
   fa.n = n;
+  fa.image = single || use_image(p, n);
   fa.kick = R(kick);
   fa.drift = R(drift);
   fa.host = hp;
@@ -630,6 +656,33 @@ hipError_t fill_tables(scf_plan* p, const scf_basis* basis) {
     if (e == hipSuccess && !p->d_dtab) e = hipMalloc((void**)&p->d_dtab, dt.size() * 8);
     if (e == hipSuccess) e = hipMemcpy(p->d_dtab, dt.data(), dt.size() * 8, hipMemcpyHostToDevice);
   }
+  {
+    // Radial weights of the operand image (FwLayout).  l >= 1: the factors of
+    // W_{k-1} and W_{k+1} in W^r_k; l = 0: 1 / kappa_k and 2 (k + lam) kappa_k.
+    const int NP = NW + 1;
+    std::vector<double> rt((size_t)L1 * 2 * NP, 0.0), bi((size_t)L1 * NP, 0.0);
+    const double ia = 1.0 / basis->alpha;
+    for (int l = 0; l <= p->lmax; ++l) {
+      const double lam = (2.0 * l + 1.0) * basis->alpha + 0.5;
+      double* r0 = &rt[(size_t)l * 2 * NP];
+      double* r1 = r0 + NP;
+      double kap = 1.0;
+      for (int k = 0; k < NP; ++k) {
+        bi[(size_t)l * NP + k] = gegen_beta(k, lam);
+        if (l == 0) {
+          r0[k] = 1.0 / kap;
+          r1[k] = 2.0 * (k + lam) * kap;
+          kap *= 2.0 * (lam + k) / (k + 1.0);
+        } else {
+          r0[k] = -0.5 * ((2.0 * l + 1.0) + (k - 1.0) * ia);
+          r1[k] = 0.5 * gegen_beta(k + 2, lam) * ((2.0 * l + 1.0) + (k + 2.0) * ia);
+        }
+      }
+    }
+    if (e == hipSuccess) e = upload_real(bi, &p->d_beta_img);
+    if (e == hipSuccess && !p->d_rtab) e = hipMalloc((void**)&p->d_rtab, rt.size() * 8);
+    if (e == hipSuccess) e = hipMemcpy(p->d_rtab, rt.data(), rt.size() * 8, hipMemcpyHostToDevice);
+  }
   return e;
 }
 
@@ -649,7 +702,7 @@ int gamma_units(const scf_plan* p, int64_t n, int64_t* stages) {
 }
 
 // Adjoint workspace: the common layout (partials sized for both passes), the
-// segment's positions X_k and force weights W_k (k = 0..nsteps), the gamma
+// segment's positions X_k and field weights W_k (k = 0..nsteps), the gamma
 // weights W', velocity and acceleration scratch, the Hessian-vector kernel's
 // block sums of every kick and the per-kick host sums S_k.
 struct AdjLayout {
@@ -664,7 +717,7 @@ AdjLayout adj_layout(const scf_plan* p, int64_t n, int nsteps) {
   int64_t st;
   const int grows = gamma_units(p, n, &st) * p->eng->gamma_rows_per_unit();
   A.L = ws_layout(p, n, 1, grows);
-  A.wsz = (size_t)(p->nmaxc + 1) * (p->lmax + 1) * (p->lmax + 1);
+  A.wsz = fw_elems(p);
   A.nblk = (n + 255) / 256;
   const size_t rs = p->rs;
   size_t off = A.L.total;
@@ -687,7 +740,7 @@ AdjLayout adj_layout(const scf_plan* p, int64_t n, int nsteps) {
 }
 
 // gamma_t = sum_i mu_i . grad b_t(x_i), mu = c (ex, ey, ez), turned into the
-// force weights W' of Eq. (total_potential) (the same scales as the forward
+// field weights W' of Eq. (total_potential) (the same scales as the forward
 // coefficients)
 template <typename R>
 scf_status run_gamma(scf_plan* p, int64_t n, const void* x, const void* y, const void* z,
@@ -714,7 +767,8 @@ scf_status run_gamma(scf_plan* p, int64_t n, const void* x, const void* y, const
     HIP_TRY(p->eng->launch_gamma(&ca, units, s));
   }
   const int rows = units * p->eng->gamma_rows_per_unit();
-  return reduce_and_finalize(p, ws + L.partials, rows, nullptr, Wout, ws, L, s);
+  return reduce_and_finalize(p, ws + L.partials, rows, nullptr, nullptr, Wout, use_image(p, n), ws,
+                             L, s);
 }
 
 bool ptr_ok(const void* q) { return q != nullptr; }

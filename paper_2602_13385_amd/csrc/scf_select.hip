@@ -268,20 +268,6 @@ __global__ void __launch_bounds__(256) axpy_kernel(int64_t n, double a, const do
 }
 
 // ---- density (Eq. total_dens) and the core of Sec. 2.1 ---------------------
-// W rows of degree l scaled by kd[l][n] (the density constants times
-// -1/(4 pi G b^2)); layout W[(l^2 + j) NW + n]
-template <typename R>
-__global__ void __launch_bounds__(256) scale_w_kernel(R* __restrict__ W, const double* __restrict__ kd,
-                                                      int lmax, int nw) {
-  const int L2 = (lmax + 1) * (lmax + 1);
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= L2 * nw) return;
-  const int n = i % nw, lj = i / nw;
-  int l = 0;
-  while ((l + 1) * (l + 1) <= lj) ++l;
-  W[i] = R((double)W[i] * kd[l * nw + n]);
-}
-
 // rho = s^(1/alpha - 2) (1 + s^(1/alpha))^(-2) psi_K, s = r/b (in place)
 template <typename R>
 __global__ void __launch_bounds__(256) density_factor_kernel(int64_t n, const R* __restrict__ x,
@@ -538,16 +524,6 @@ hipError_t launch_delta_compact(int dtype, int64_t n, const void* w0, const void
 hipError_t launch_axpy(int64_t n, double a, const double* x, double* y, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   axpy_kernel<<<blocks_of(n), 256, 0, s>>>(n, a, x, y);
-  return hipGetLastError();
-}
-
-hipError_t launch_scale_w(int dtype, void* W, const double* kd, int lmax, int nmaxc,
-                          hipStream_t s) {
-  const int nw = nmaxc + 1, cnt = (lmax + 1) * (lmax + 1) * nw;
-  if (dtype == 0)
-    scale_w_kernel<float><<<blocks_of(cnt), 256, 0, s>>>((float*)W, kd, lmax, nw);
-  else
-    scale_w_kernel<double><<<blocks_of(cnt), 256, 0, s>>>((double*)W, kd, lmax, nw);
   return hipGetLastError();
 }
 

@@ -32,122 +32,157 @@ __global__ void __launch_bounds__(256) reduce_kernel(const R* __restrict__ parti
     red1[(int64_t)blockIdx.y * T + t] = ((sh[0][ti] + sh[1][ti]) + sh[2][ti]) + sh[3][ti];
 }
 
-// a_t = cs_t * (sum of the chunk sums of t), in a fixed order (4 strided
-// chunk subsets, then their sum), and the force weights W[(l,j)][n] =
-// fw_t a_t; rows n in (nmax, nmaxc] of W are zero.
+// Field weights of row (l, j) from its force weights: lane k of a wave holds
+// W_k (zero for k > nmaxc) and forms the k-th weights, k < nmaxc + 2.  The
+// radial weights come from the rounded force weights, in double precision.
+// r0, r1: the lane's two factors (WeightTables.rtab).
 template <typename R>
-__device__ __forceinline__ void finalize_block(const double* __restrict__ red1, int nchunks, int T,
-                                               int nmax, int lmax, int nmaxc,
-                                               const double* __restrict__ cs,
-                                               const double* __restrict__ fw, double* coef, R* W,
-                                               int cb, int ncb) {
-  __shared__ double sh[4][64];
-  const int L2 = (lmax + 1) * (lmax + 1);
-  const int ti = threadIdx.x & 63, kc = threadIdx.x >> 6;
-  const int t = cb * 64 + ti;
-  double s = 0.0;
-  if (t < T) {
-#pragma unroll 8
-    for (int c = kc; c < nchunks; c += 4) s += red1[(int64_t)c * T + t];
+__device__ __forceinline__ void emit_row(const R wk, const double r0, const double r1,
+                                         const int lj, const int k, const WeightTables& wt, R* FW) {
+  const int nc = wt.nmaxc;
+  if (k <= nc) FW[lj * (nc + 1) + k] = wk;
+  if constexpr (sizeof(R) == 4) {
+    if (!wt.image) return;
+    const int l = (int)sqrtf((float)lj + 0.5f), j = lj - l * l, m = (j + 1) >> 1;
+    double v;
+    if (l == 0) {
+      const double u = k <= nc ? (double)wk * r0 : 0.0;
+      v = 0.0;
+      for (int n = 1; n <= nc; ++n) {
+        const double un = __shfl(u, n, 64);
+        if (n > k && ((n - k) & 1)) v += un;
+      }
+      v *= r1;
+    } else {
+      const R wm = __shfl_up(wk, 1, 64), wp = __shfl_down(wk, 1, 64);
+      v = -0.5 * (double)wk;
+      if (k > 0) v += r0 * (double)wm;
+      if (k < nc) v += r1 * (double)wp;
+    }
+    if (k < nc + 2) {
+      // cosine part in lanes 0, 1 of the quadruple, sine part (even j > 0) in 2, 3
+      const int q = m * (nc + 2) + k;
+      R* d = FW + FwLayout::img0(nc, wt.lmax) + 64 * (FwLayout::off(l, nc) + (q >> 4)) +
+             4 * (q & 15) + ((j > 0 && (j & 1) == 0) ? 2 : 0);
+      d[0] = wk;
+      d[1] = R(v);
+    }
   }
-  sh[kc][ti] = s;
-  __syncthreads();
-  if (kc == 0 && t < T) {
-    const double tot = ((sh[0][ti] + sh[1][ti]) + sh[2][ti]) + sh[3][ti];
-    const int n = t / L2, lj = t % L2;
-    const double cv = cs[t] * tot;
-    if (coef) coef[t] = cv;
-    W[lj * (nmaxc + 1) + n] = R(fw[t] * cv);
-  }
-  const int npad = (nmaxc - nmax) * L2;
-  for (int q = cb * blockDim.x + threadIdx.x; q < npad; q += ncb * blockDim.x) {
-    const int n = nmax + 1 + q / L2, lj = q % L2;
-    W[lj * (nmaxc + 1) + n] = R(0);
+}
+// lane k's factors of row (l, j)
+__device__ __forceinline__ void row_factors(const WeightTables& wt, const int lj, const int k,
+                                            double& r0, double& r1) {
+  const int l = (int)sqrtf((float)lj + 0.5f), NP = wt.nmaxc + 2;
+  r0 = r1 = 0.0;
+  if (wt.image && k < NP) {
+    r0 = wt.rtab[(2 * l) * NP + k];
+    r1 = wt.rtab[(2 * l + 1) * NP + k];
   }
 }
 
-// Single-pass reduction and finalisation of up to a few thousand partial
-// rows [r0, r1), for a block of 1024 threads and the 16 coefficients
-// t = 16 cb .. 16 cb + 15: thread (g, c) sums rows r0 + g, r0 + g + 64, ..
-// of coefficient 16 cb + c in double precision (each wave reads four 64-byte
-// row pieces per load), the 64 row-group sums of a coefficient are then added
-// pairwise in a fixed order, and a_t = cs_t * sum and W[(l,j)][n] = fw_t a_t
-// are written; rows n in (nmax, nmaxc] of W are zero.
-template <typename R>
-__device__ __forceinline__ void reduce_final_cols(const R* __restrict__ partials, int r0, int r1,
-                                                  int T, int nmax, int lmax, int nmaxc,
-                                                  const double* __restrict__ cs,
-                                                  const double* __restrict__ fw, double* coef,
-                                                  R* W, int cb, int ncb) {
-  __shared__ double sh[64][16];
-  const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int t = cb * 16 + c;
+// Reduction and finalisation of the partial rows [r0, r1) for one row (l, j):
+// a block of NT threads takes the row's NC = nmax + 1 <= CW coefficients
+// (which lie next to each other in a partial row); thread (g, n) sums partial
+// rows r0 + g, r0 + g + G, .. (G = NT / CW row groups) in double precision.
+// The row groups of a wave are added by lane exchanges, those of the waves
+// through LDS by wave 0 (a fixed order), which then holds the row in its lanes:
+// a_t = cs_t * sum and the weights follow without another barrier.  One block
+// per (l, j) rather than per 16 consecutive coefficients, so that it has the
+// neighbours n - 1, n + 1 that the radial weights need.
+template <int NT, int CW, typename IN, typename R>
+__device__ __forceinline__ void reduce_final_row(const IN* __restrict__ partials, int r0, int r1,
+                                                 const WeightTables& wt, double* coef, R* W,
+                                                 R* FW, int lj) {
+  constexpr int G = NT / CW, GW = 64 / CW;  // row groups of the block, of a wave
+  __shared__ double sh[NT / 64][CW];
+  const int L2 = (wt.lmax + 1) * (wt.lmax + 1), NC = wt.nmax + 1, T = NC * L2;
+  const int tid = threadIdx.x, lane = tid & 63, g = tid / CW, c = tid % CW;
+  // wave 0's factors, loaded before the sums
+  double f0 = 0.0, f1 = 0.0, cs = 0.0, fw = 0.0;
+  if (tid < 64) {
+    row_factors(wt, lj, lane, f0, f1);
+    if (c < NC) {
+      cs = wt.cs[c * L2 + lj];
+      fw = wt.fw[c * L2 + lj];
+    }
+  }
   double s = 0.0;
-  if (t < T) {
+  if (c < NC) {
+    const IN* __restrict__ col = partials + lj * NC + c;
 #pragma unroll 8
-    for (int b = r0 + g; b < r1; b += 64) s += double(partials[(int64_t)b * T + t]);
+    for (int b = r0 + g; b < r1; b += G) s += double(col[(int64_t)b * T]);
   }
-  sh[g][c] = s;
+#pragma unroll
+  for (int o = 32; o >= CW; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (lane < CW) sh[tid >> 6][lane] = s;
   __syncthreads();
-  for (int h = 32; h >= 1; h >>= 1) {
-    if (g < h) sh[g][c] += sh[g + h][c];
-    __syncthreads();
+  if (tid >= 64) return;
+  s = 0.0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; w += GW) s += sh[w + lane / CW][c];
+#pragma unroll
+  for (int o = 32; o >= CW; o >>= 1) s += __shfl_xor(s, o, 64);
+  R wk = R(0);
+  if (lane < NC) {
+    const double cv = cs * s;
+    if (coef) coef[lane * L2 + lj] = cv;
+    wk = R(fw * cv);
   }
-  const int L2 = (lmax + 1) * (lmax + 1);
-  if (g == 0 && t < T) {
-    const int n = t / L2, lj = t % L2;
-    const double cv = cs[t] * sh[0][c];
-    if (coef) coef[t] = cv;
-    W[lj * (nmaxc + 1) + n] = R(fw[t] * cv);
-  }
-  const int npad = (nmaxc - nmax) * L2;
-  for (int q = cb * blockDim.x + threadIdx.x; q < npad; q += ncb * blockDim.x) {
-    const int n = nmax + 1 + q / L2, lj = q % L2;
-    W[lj * (nmaxc + 1) + n] = R(0);
-  }
+  if (W && lane <= wt.nmaxc) W[lj * (wt.nmaxc + 1) + lane] = wk;
+  emit_row<R>(wk, f0, f1, lj, lane, wt, FW);
 }
 
-// Coefficient chunk of a block: blocks are dealt to the 8 XCDs in turn
-// (block b runs on XCD b mod 8), so chunk (b mod 8) per + b / 8 gives each
-// XCD a contiguous range of chunks, and the two 64-byte halves of a row's
-// 128-byte line are read through one L2 (the grid is a multiple of 8 blocks).
-__device__ __forceinline__ int xcd_chunk() {
+// Row (l, j) of a block: blocks are dealt to the 8 XCDs in turn (block b runs
+// on XCD b mod 8), so row (b mod 8) per + b / 8 gives each XCD a contiguous
+// range of rows, and the pieces of a 128-byte line of the partial rows are read
+// through one L2 (the grid is a multiple of 8 blocks).
+__device__ __forceinline__ int xcd_row() {
   const int per = gridDim.x >> 3;
   return (blockIdx.x & 7) * per + (blockIdx.x >> 3);
 }
-constexpr int grid_chunks(int T) { return ((T + 15) / 16 + 7) / 8 * 8; }
+constexpr int grid_rows(int L2) { return (L2 + 7) / 8 * 8; }
 
-template <typename R>
-__global__ void __launch_bounds__(1024) reduce_final_small_kernel(
-    const R* __restrict__ partials, int nblocks, int T, int nmax, int lmax, int nmaxc,
-    const double* __restrict__ cs, const double* __restrict__ fw, double* coef, R* W) {
-  reduce_final_cols<R>(partials, 0, nblocks, T, nmax, lmax, nmaxc, cs, fw, coef, W, xcd_chunk(),
-                       gridDim.x);
+template <int NT, typename IN, typename R>
+__global__ void __launch_bounds__(NT) reduce_final_kernel(const IN* __restrict__ partials,
+                                                            int nrows, WeightTables wt,
+                                                            double* coef, R* W, R* FW) {
+  const int lj = xcd_row();
+  if (lj >= (wt.lmax + 1) * (wt.lmax + 1)) return;
+  if (wt.nmax < 16)
+    reduce_final_row<NT, 16, IN, R>(partials, 0, nrows, wt, coef, W, FW, lj);
+  else
+    reduce_final_row<NT, 32, IN, R>(partials, 0, nrows, wt, coef, W, FW, lj);
 }
 
+// one block (a wave) per row (l, j)
 template <typename R>
-__global__ void __launch_bounds__(256) finalize_kernel(const double* __restrict__ red1, int nchunks,
-                                                       int T, int nmax, int lmax, int nmaxc,
-                                                       const double* __restrict__ cs,
-                                                       const double* __restrict__ fw, double* coef,
-                                                       R* W) {
-  finalize_block<R>(red1, nchunks, T, nmax, lmax, nmaxc, cs, fw, coef, W, blockIdx.x, gridDim.x);
-}
-
-template <typename R>
-__global__ void __launch_bounds__(256) make_w_kernel(const double* __restrict__ coef, int T, int nmax,
-                                                     int lmax, int nmaxc,
-                                                     const double* __restrict__ fw, R* W) {
-  const int L2 = (lmax + 1) * (lmax + 1);
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (nmaxc + 1) * L2) return;
-  const int lj = e / (nmaxc + 1), n = e % (nmaxc + 1);
-  if (n > nmax) {
-    W[e] = R(0);
-    return;
+__global__ void __launch_bounds__(64) make_w_kernel(const double* __restrict__ coef,
+                                                    WeightTables wt,
+                                                    const double* __restrict__ kd, R* FW) {
+  const int lj = blockIdx.x, n = threadIdx.x, L2 = (wt.lmax + 1) * (wt.lmax + 1);
+  double f0, f1;
+  row_factors(wt, lj, n, f0, f1);
+  R v = R(0);
+  if (n <= wt.nmax) {
+    const int t = n * L2 + lj;
+    v = R(wt.fw[t] * coef[t]);
+    if (kd) {
+      const int l = (int)sqrtf((float)lj + 0.5f);
+      v = R((double)v * kd[l * (wt.nmaxc + 1) + n]);
+    }
   }
-  const int t = n * L2 + lj;
-  W[e] = R(fw[t] * coef[t]);
+  emit_row<R>(v, f0, f1, lj, n, wt, FW);
+}
+
+template <typename R>
+__global__ void __launch_bounds__(64) expand_w_kernel(const R* __restrict__ W, WeightTables wt,
+                                                      R* FW, int64_t W_stride) {
+  const int lj = blockIdx.x, n = threadIdx.x, NW = wt.nmaxc + 1;
+  const int64_t k = blockIdx.y;
+  double f0, f1;
+  row_factors(wt, lj, n, f0, f1);
+  const R v = n < NW ? W[(k * gridDim.x + lj) * NW + n] : R(0);
+  emit_row<R>(v, f0, f1, lj, n, wt, FW + k * W_stride);
 }
 
 template <typename R>
@@ -190,14 +225,15 @@ __global__ void __launch_bounds__(256) reduce_batched_kernel(const R* __restrict
         ((sh[0][ti] + sh[1][ti]) + sh[2][ti]) + sh[3][ti];
 }
 
-// Batched finalisation: coef[c][t] and W[c][.] of every cluster.  Block
-// (0, 0) also copies row *step of the centre table into cur (the rows the
-// field pass of this step reads) and then advances *step.
-template <typename R>
-__global__ void __launch_bounds__(256) finalize_batched_kernel(
-    const double* __restrict__ red1, int nchunks, int T, int nmax, int lmax, int nmaxc,
-    const double* __restrict__ cs, const double* __restrict__ fw, double* coef, R* W,
-    int64_t W_stride, const double* __restrict__ centre_tab, int ncl, double* cur, int* step) {
+// Batched reduction and finalisation: block (lj, c) reduces cluster c's rows
+// (rows[c] .. rows[c+1], or its nchunks chunk sums) as reduce_final_row does;
+// block (0, 0) also copies row *step of the centre table into cur (the rows
+// the field pass of this step reads) and then advances *step.
+template <int NT, typename IN, typename R>
+__global__ void __launch_bounds__(NT) reduce_final_batched_kernel(
+    const IN* __restrict__ partials, const int32_t* __restrict__ rows, int nchunks,
+    WeightTables wt, double* coef, R* FW, int64_t W_stride, const double* __restrict__ centre_tab,
+    int ncl, double* cur, int* step) {
   const int c = blockIdx.y;
   if (blockIdx.x == 0 && c == 0 && step) {
     const int k = *step;
@@ -206,31 +242,15 @@ __global__ void __launch_bounds__(256) finalize_batched_kernel(
     __syncthreads();
     if (threadIdx.x == 0) *step = k + 1;
   }
-  finalize_block<R>(red1 + (int64_t)c * nchunks * T, nchunks, T, nmax, lmax, nmaxc, cs, fw,
-                    coef ? coef + (int64_t)c * T : nullptr, W + (int64_t)c * W_stride, blockIdx.x,
-                    gridDim.x);
-}
-
-// Batched single-pass reduction and finalisation: block (cb, c) reduces
-// cluster c's rows [rows[c], rows[c+1]) for coefficients 16 cb .. 16 cb + 15
-// (as reduce_final_cols); block (0, 0) also copies row *step of the centre
-// table into cur and then advances *step (as finalize_batched_kernel).
-template <typename R>
-__global__ void __launch_bounds__(1024) reduce_final_batched_kernel(
-    const R* __restrict__ partials, const int32_t* __restrict__ rows, int T, int nmax, int lmax,
-    int nmaxc, const double* __restrict__ cs, const double* __restrict__ fw, double* coef, R* W,
-    int64_t W_stride, const double* __restrict__ centre_tab, int ncl, double* cur, int* step) {
-  const int c = blockIdx.y;
-  if (blockIdx.x == 0 && c == 0 && step) {
-    const int k = *step;
-    for (int i = threadIdx.x; i < ncl * 9; i += blockDim.x)
-      cur[i] = centre_tab[(int64_t)k * ncl * 9 + i];
-    __syncthreads();
-    if (threadIdx.x == 0) *step = k + 1;
-  }
-  reduce_final_cols<R>(partials, rows[c], rows[c + 1], T, nmax, lmax, nmaxc, cs, fw,
-                       coef ? coef + (int64_t)c * T : nullptr, W + (int64_t)c * W_stride,
-                       xcd_chunk(), gridDim.x);
+  const int lj = xcd_row(), L2 = (wt.lmax + 1) * (wt.lmax + 1);
+  if (lj >= L2) return;
+  const int r0 = nchunks ? c * nchunks : rows[c], r1 = nchunks ? r0 + nchunks : rows[c + 1];
+  double* cf = coef ? coef + (int64_t)c * (wt.nmax + 1) * L2 : nullptr;
+  R* fwc = FW + (int64_t)c * W_stride;
+  if (wt.nmax < 16)
+    reduce_final_row<NT, 16, IN, R>(partials, r0, r1, wt, cf, (R*)nullptr, fwc, lj);
+  else
+    reduce_final_row<NT, 32, IN, R>(partials, r0, r1, wt, cf, (R*)nullptr, fwc, lj);
 }
 
 __global__ void set_int_kernel(int* p, int v) {
@@ -254,42 +274,65 @@ hipError_t launch_reduce(int dtype, const void* partials, int nblocks, int T, in
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_final_small(int dtype, const void* partials, int nblocks, int T, int nmax,
-                                    int lmax, int nmaxc, const double* cs, const double* fw,
-                                    double* coef, void* W, hipStream_t s) {
-  if (T <= 0) return hipSuccess;
-  const int grid = grid_chunks(T);
-  if (dtype == 0)
-    reduce_final_small_kernel<float><<<grid, 1024, 0, s>>>((const float*)partials, nblocks, T, nmax,
-                                                           lmax, nmaxc, cs, fw, coef, (float*)W);
+// Threads per block, input and real type of a reduction: 256 threads (16 row
+// groups) up to kFewRows partial rows, where the rest of 1024 would have no row
+// to add and the batched step has many such blocks; with 90 rows the larger
+// block is already the faster one (coefficients and reduction of 1e4 points,
+// nmax 6, lmax 4: 8.6 against 9.6 us).
+constexpr int kFewRows = 32;
+template <typename F>
+static void with_reduce_types(int dtype, bool chunks_f64, int rows, F f) {
+  using T4 = std::integral_constant<int, 256>;
+  using T16 = std::integral_constant<int, 1024>;
+  const bool few = rows <= kFewRows;
+  if (dtype == 0 && !chunks_f64)
+    few ? f(T4{}, float(0), float(0)) : f(T16{}, float(0), float(0));
+  else if (dtype == 0)
+    few ? f(T4{}, double(0), float(0)) : f(T16{}, double(0), float(0));
   else
-    reduce_final_small_kernel<double><<<grid, 1024, 0, s>>>((const double*)partials, nblocks, T,
-                                                            nmax, lmax, nmaxc, cs, fw, coef,
-                                                            (double*)W);
+    few ? f(T4{}, double(0), double(0)) : f(T16{}, double(0), double(0));
+}
+
+hipError_t launch_reduce_final(int dtype, bool chunks_f64, const void* partials, int nrows,
+                               const WeightTables& wt, double* coef, void* W, void* FW,
+                               hipStream_t s) {
+  const int grid = grid_rows((wt.lmax + 1) * (wt.lmax + 1));
+  with_reduce_types(dtype, chunks_f64, nrows, [&](auto nt, auto in, auto r) {
+    using IN = decltype(in);
+    using R = decltype(r);
+    constexpr int NT = decltype(nt)::value;
+    reduce_final_kernel<NT, IN, R><<<grid, NT, 0, s>>>((const IN*)partials, nrows, wt, coef, (R*)W,
+                                                       (R*)FW);
+  });
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(int dtype, const double* red1, int nchunks, int T, int nmax, int lmax,
-                           int nmaxc, const double* cs, const double* fw, double* coef, void* W,
+hipError_t launch_make_w(int dtype, const double* coef, const WeightTables& wt, const double* kd,
+                         void* FW, hipStream_t s) {
+  const int grid = (wt.lmax + 1) * (wt.lmax + 1);
+  if (dtype == 0)
+    make_w_kernel<float><<<grid, 64, 0, s>>>(coef, wt, kd, (float*)FW);
+  else
+    make_w_kernel<double><<<grid, 64, 0, s>>>(coef, wt, kd, (double*)FW);
+  return hipGetLastError();
+}
+
+hipError_t launch_expand_w(int dtype, const void* W, int rows, const WeightTables& wt, void* FW,
                            hipStream_t s) {
-  const int grid = (T + 63) / 64;
-  if (dtype == 0)
-    finalize_kernel<float><<<grid, 256, 0, s>>>(red1, nchunks, T, nmax, lmax, nmaxc, cs, fw, coef,
-                                                (float*)W);
-  else
-    finalize_kernel<double><<<grid, 256, 0, s>>>(red1, nchunks, T, nmax, lmax, nmaxc, cs, fw, coef,
-                                                 (double*)W);
-  return hipGetLastError();
-}
-
-hipError_t launch_make_w(int dtype, const double* coef, int T, int nmax, int lmax, int nmaxc,
-                         const double* fw, void* W, hipStream_t s) {
-  const int ne = (nmaxc + 1) * (lmax + 1) * (lmax + 1);
-  const int grid = (ne + 255) / 256;
-  if (dtype == 0)
-    make_w_kernel<float><<<grid, 256, 0, s>>>(coef, T, nmax, lmax, nmaxc, fw, (float*)W);
-  else
-    make_w_kernel<double><<<grid, 256, 0, s>>>(coef, T, nmax, lmax, nmaxc, fw, (double*)W);
+  if (rows <= 0) return hipSuccess;
+  const int64_t stride = FwLayout::elems(wt.nmaxc, wt.lmax, dtype == 0);
+  const int L2 = (wt.lmax + 1) * (wt.lmax + 1);
+  // (at most 65535 rows per launch: the grid's y limit)
+  for (int k0 = 0; k0 < rows; k0 += 65535) {
+    const dim3 grid(L2, rows - k0 < 65535 ? rows - k0 : 65535);
+    const int64_t wo = (int64_t)k0 * L2 * (wt.nmaxc + 1);
+    if (dtype == 0)
+      expand_w_kernel<float><<<grid, 64, 0, s>>>((const float*)W + wo, wt,
+                                                 (float*)FW + k0 * stride, stride);
+    else
+      expand_w_kernel<double><<<grid, 64, 0, s>>>((const double*)W + wo, wt,
+                                                  (double*)FW + k0 * stride, stride);
+  }
   return hipGetLastError();
 }
 
@@ -321,39 +364,21 @@ hipError_t launch_reduce_batched(int dtype, const void* partials, const int32_t*
   return hipGetLastError();
 }
 
-hipError_t launch_finalize_batched(int dtype, const double* red1, int nchunks, int T, int nmax,
-                                   int lmax, int nmaxc, const double* cs, const double* fw,
-                                   double* coef, void* W, int64_t W_stride,
-                                   const double* centre_tab, int ncl, double* cur, int* step,
-                                   hipStream_t s) {
+hipError_t launch_reduce_final_batched(int dtype, bool chunks_f64, const void* partials,
+                                      const int32_t* rows, int nchunks, int max_rows, int ncl,
+                                      const WeightTables& wt, double* coef, void* FW,
+                                      int64_t W_stride, const double* centre_tab, double* cur,
+                                      int* step, hipStream_t s) {
   if (ncl <= 0) return hipSuccess;
-  dim3 grid((T + 63) / 64, ncl);
-  if (dtype == 0)
-    finalize_batched_kernel<float><<<grid, 256, 0, s>>>(red1, nchunks, T, nmax, lmax, nmaxc, cs, fw,
-                                                        coef, (float*)W, W_stride, centre_tab, ncl,
-                                                        cur, step);
-  else
-    finalize_batched_kernel<double><<<grid, 256, 0, s>>>(red1, nchunks, T, nmax, lmax, nmaxc, cs,
-                                                         fw, coef, (double*)W, W_stride,
-                                                         centre_tab, ncl, cur, step);
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_final_batched(int dtype, const void* partials, const int32_t* rows, int ncl,
-                                      int T, int nmax, int lmax, int nmaxc, const double* cs,
-                                      const double* fw, double* coef, void* W, int64_t W_stride,
-                                      const double* centre_tab, double* cur, int* step,
-                                      hipStream_t s) {
-  if (ncl <= 0 || T <= 0) return hipSuccess;
-  dim3 grid(grid_chunks(T), ncl);
-  if (dtype == 0)
-    reduce_final_batched_kernel<float><<<grid, 1024, 0, s>>>(
-        (const float*)partials, rows, T, nmax, lmax, nmaxc, cs, fw, coef, (float*)W, W_stride,
-        centre_tab, ncl, cur, step);
-  else
-    reduce_final_batched_kernel<double><<<grid, 1024, 0, s>>>(
-        (const double*)partials, rows, T, nmax, lmax, nmaxc, cs, fw, coef, (double*)W, W_stride,
-        centre_tab, ncl, cur, step);
+  const dim3 grid(grid_rows((wt.lmax + 1) * (wt.lmax + 1)), ncl);
+  const int nch = chunks_f64 ? nchunks : 0;
+  with_reduce_types(dtype, chunks_f64, max_rows, [&](auto nt, auto in, auto r) {
+    using IN = decltype(in);
+    using R = decltype(r);
+    constexpr int NT = decltype(nt)::value;
+    reduce_final_batched_kernel<NT, IN, R><<<grid, NT, 0, s>>>(
+        (const IN*)partials, rows, nch, wt, coef, (R*)FW, W_stride, centre_tab, ncl, cur, step);
+  });
   return hipGetLastError();
 }
 
