@@ -302,8 +302,7 @@ void scf_plan_destroy(scf_plan* p) {
   if (p->gexec_g) (void)hipGraphExecDestroy(p->gexec_g);
   if (p->graph_g) (void)hipGraphDestroy(p->graph_g);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
-  if (p->h_tab) (void)hipHostFree(p->h_tab);
-  if (p->h_meta) (void)hipHostFree(p->h_meta);
+  if (p->h_stage) (void)hipHostFree(p->h_stage);
   if (p->d_beta_rad) (void)hipFree(p->d_beta_rad);
   if (p->d_beta_ang) (void)hipFree(p->d_beta_ang);
   if (p->d_kden) (void)hipFree(p->d_kden);
@@ -561,70 +560,81 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     stg[c] = (offsets[c + 1] - offsets[c] + P - 1) / P;
     st_tot += stg[c];
   }
-  std::vector<int64_t> sb, se;
-  std::vector<int32_t> slot, unit_start(ncl + 1, 0), rows(ncl + 1, 0), bcl;
-  std::vector<int64_t> bb, be;
-  int64_t max_stages = 0;
+  // wave-units of cluster c: in proportion to its stages, one round in all
+  std::vector<int> uc(ncl), rows(ncl + 1, 0);
+  int64_t max_stages = 0, U = 0, nblk = 0;
   for (int c = 0; c < ncl; ++c) {
-    unit_start[c] = (int32_t)sb.size();
+    uc[c] = 0;
+    nblk += (offsets[c + 1] - offsets[c] + 255) / 256;
     if (stg[c] == 0) continue;
-    int64_t uc = (int64_t)((double)cap * (double)stg[c] / (double)st_tot);
-    uc = std::max<int64_t>(1, std::min<int64_t>(uc, stg[c]));
-    for (int64_t u = 0; u < uc; ++u) {
-      const int64_t s0 = stg[c] * u / uc, s1 = stg[c] * (u + 1) / uc;
-      sb.push_back(offsets[c] + s0 * P);
-      se.push_back(std::min(offsets[c] + s1 * P, offsets[c + 1]));
-      slot.push_back((int32_t)slot.size());
-      max_stages = std::max(max_stages, s1 - s0);
-    }
+    const int64_t u = (int64_t)((double)cap * (double)stg[c] / (double)st_tot);
+    uc[c] = (int)std::max<int64_t>(1, std::min<int64_t>(u, stg[c]));
+    U += uc[c];
+    max_stages = std::max(max_stages, (stg[c] + uc[c] - 1) / uc[c]);
   }
-  unit_start[ncl] = (int32_t)sb.size();
   // partial rows of cluster c: [rows[c], rows[c+1])
   const int rpu = unit_rows(p, v, max_stages);
-  for (int c = 0; c <= ncl; ++c) rows[c] = unit_start[c] * rpu;
-  for (int c = 0; c < ncl; ++c)
-    for (int64_t b0 = offsets[c]; b0 < offsets[c + 1]; b0 += 256) {
-      bcl.push_back(c);
-      bb.push_back(b0);
-      be.push_back(std::min(b0 + 256, offsets[c + 1]));
-    }
-  const int U = (int)sb.size();
-  const int64_t nblk = (int64_t)bcl.size();
+  for (int c = 0; c < ncl; ++c) rows[c + 1] = rows[c] + uc[c] * rpu;
   if (U > B.max_units || nblk > B.max_blocks)
     return fail(SCF_ERR_INVALID_ARG, "internal: work list larger than its workspace");
+  // (centre row 0 is used only for a(x0))
+  const int64_t nrows = (int64_t)nsteps + 1, row0 = acc_valid ? 1 : 0;
+  const int64_t crows = std::min<int64_t>(kCentreRows, nrows - row0);
+  const BatchUpload up(U, ncl, nblk, crows);
 
-  // ---- centre orbit (host, double): rows k = 0..nsteps of R, grad psi_host(R)
-  const int64_t nrows = (int64_t)nsteps + 1;
-  const size_t tab_elems = (size_t)nrows * ncl * 9;
-  const size_t meta_bytes = (size_t)U * 20 + (size_t)(ncl + 1) * 4 + (size_t)nblk * 20;
+  // ---- staging (pinned): the upload with the whole centre table at its end ----
+  const size_t stage_bytes = up.tab + (size_t)nrows * ncl * 9 * sizeof(double);
   if (p->staging_pending) {
     HIP_TRY(hipEventSynchronize(p->ev_staging));
     p->staging_pending = false;
   }
-  if (p->h_tab_cap < tab_elems) {
-    if (p->h_tab) HIP_TRY(hipHostFree(p->h_tab));
-    p->h_tab = nullptr;
-    p->h_tab_cap = 0;
-    HIP_TRY(hipHostMalloc((void**)&p->h_tab, tab_elems * sizeof(double), hipHostMallocDefault));
-    p->h_tab_cap = tab_elems;
-  }
-  if (p->h_meta_cap < meta_bytes) {
-    if (p->h_meta) HIP_TRY(hipHostFree(p->h_meta));
-    p->h_meta = nullptr;
-    p->h_meta_cap = 0;
-    HIP_TRY(hipHostMalloc((void**)&p->h_meta, meta_bytes, hipHostMallocDefault));
-    p->h_meta_cap = meta_bytes;
+  if (p->h_stage_cap < stage_bytes) {
+    if (p->h_stage) HIP_TRY(hipHostFree(p->h_stage));
+    p->h_stage = nullptr;
+    p->h_stage_cap = 0;
+    HIP_TRY(hipHostMalloc((void**)&p->h_stage, stage_bytes, hipHostMallocDefault));
+    p->h_stage_cap = stage_bytes;
   }
   if (!p->ev_staging) HIP_TRY(hipEventCreateWithFlags(&p->ev_staging, hipEventDisableTiming));
+  char* hs_ = p->h_stage;
+  *(int*)(hs_ + up.ctr) = 0;
+  {
+    int64_t* sb = (int64_t*)(hs_ + up.seg_begin);
+    int64_t* se = (int64_t*)(hs_ + up.seg_end);
+    int32_t* slot = (int32_t*)(hs_ + up.seg_slot);
+    int32_t* bcl = (int32_t*)(hs_ + up.blk_cluster);
+    int64_t* bb = (int64_t*)(hs_ + up.blk_begin);
+    int64_t* be = (int64_t*)(hs_ + up.blk_end);
+    int64_t i = 0, q = 0;
+    for (int c = 0; c < ncl; ++c) {
+      for (int64_t u = 0; u < uc[c]; ++u, ++i) {
+        sb[i] = offsets[c] + (stg[c] * u / uc[c]) * P;
+        se[i] = std::min(offsets[c] + (stg[c] * (u + 1) / uc[c]) * P, offsets[c + 1]);
+        slot[i] = (int32_t)i;
+      }
+      for (int64_t b0 = offsets[c]; b0 < offsets[c + 1]; b0 += 256, ++q) {
+        bcl[q] = c;
+        bb[q] = b0;
+        be[q] = std::min(b0 + 256, offsets[c + 1]);
+      }
+    }
+    std::memcpy(hs_ + up.rows, rows.data(), (size_t)(ncl + 1) * 4);
+  }
+
+  // ---- centre orbit (host, double): rows k = row0..nsteps of R, grad psi_host(R)
+  double* tab = (double*)(hs_ + up.tab);
   const double h = 0.5 * dt;
   std::vector<double> cnew(6 * (size_t)ncl);
   for (int c = 0; c < ncl; ++c) {
     double R[3] = {centres[6 * c], centres[6 * c + 1], centres[6 * c + 2]};
     double V[3] = {centres[6 * c + 3], centres[6 * c + 4], centres[6 * c + 5]};
+    // grad psi_host at R, and its table row
+    double g[3];
     auto put_row = [&](int64_t k) {
-      double g[3] = {0, 0, 0};
+      g[0] = g[1] = g[2] = 0.0;
       if (with_host) host_grad<double>(hd, R[0], R[1], R[2], g[0], g[1], g[2]);
-      double* row = p->h_tab + ((size_t)k * ncl + c) * 9;
+      if (k < row0) return;
+      double* row = tab + ((size_t)(k - row0) * ncl + c) * 9;
       for (int i = 0; i < 3; ++i) {
         row[i] = R[i];
         row[3 + i] = g[i];
@@ -633,15 +643,13 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     };
     put_row(0);
     if (nsteps > 0) {
-      double gc[3];
-      centre_accel(hd, R, gc);
-      for (int i = 0; i < 3; ++i) V[i] += h * gc[i];
+      // (the centre's acceleration is -g of the row just put)
+      for (int i = 0; i < 3; ++i) V[i] += h * -g[i];
       for (int i = 0; i < 3; ++i) R[i] += dt * V[i];
       for (int k = 1; k <= nsteps; ++k) {
         const bool last = k == nsteps;
         put_row(k);
-        centre_accel(hd, R, gc);
-        for (int i = 0; i < 3; ++i) V[i] += (last ? h : dt) * gc[i];
+        for (int i = 0; i < 3; ++i) V[i] += (last ? h : dt) * -g[i];
         if (!last)
           for (int i = 0; i < 3; ++i) R[i] += dt * V[i];
       }
@@ -651,43 +659,30 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
       cnew[6 * c + 3 + i] = V[i];
     }
   }
-  {
-    char* q = p->h_meta;
-    auto put = [&](const void* src, size_t bytes) {
-      if (bytes) std::memcpy(q, src, bytes);
-      q += bytes;
-    };
-    put(sb.data(), (size_t)U * 8);
-    put(se.data(), (size_t)U * 8);
-    put(slot.data(), (size_t)U * 4);
-    put(rows.data(), (size_t)(ncl + 1) * 4);
-    put(bcl.data(), (size_t)nblk * 4);
-    put(bb.data(), (size_t)nblk * 8);
-    put(be.data(), (size_t)nblk * 8);
-    const char* q0 = p->h_meta;
-    size_t o = 0;
-    auto up = [&](size_t dst, size_t bytes) -> hipError_t {
-      hipError_t e = bytes ? hipMemcpyAsync(w + dst, q0 + o, bytes, hipMemcpyHostToDevice, s)
-                           : hipSuccess;
-      o += bytes;
-      return e;
-    };
-    HIP_TRY(up(B.seg_begin, (size_t)U * 8));
-    HIP_TRY(up(B.seg_end, (size_t)U * 8));
-    HIP_TRY(up(B.seg_slot, (size_t)U * 4));
-    HIP_TRY(up(B.rows, (size_t)(ncl + 1) * 4));
-    HIP_TRY(up(B.blk_cluster, (size_t)nblk * 4));
-    HIP_TRY(up(B.blk_begin, (size_t)nblk * 8));
-    HIP_TRY(up(B.blk_end, (size_t)nblk * 8));
+  char* dev = w + B.up;
+  // one copy: counter, work lists and the first centre rows
+  HIP_TRY(hipMemcpyAsync(dev, hs_, up.tab + (size_t)crows * ncl * 9 * sizeof(double),
+                         hipMemcpyHostToDevice, s));
+  // The staging may be refilled once the copies out of it are done: marked
+  // after the last of them, not at the end of the call, so that the next call's
+  // host work overlaps this call's kernels.
+  auto staged = [&]() -> scf_status {
+    HIP_TRY(hipEventRecord(p->ev_staging, s));
+    p->staging_pending = true;
+    return SCF_OK;
+  };
+  if (nrows - row0 <= kCentreRows) {
+    scf_status ss = staged();
+    if (ss != SCF_OK) return ss;
   }
   // uploads rows [k0, k0 + kCentreRows) of the centre table and restarts the
   // device row counter
   auto upload_rows = [&](int64_t k0) -> scf_status {
     const int64_t k1 = std::min<int64_t>(k0 + kCentreRows, nrows);
-    HIP_TRY(hipMemcpyAsync(w + B.tab, p->h_tab + (size_t)k0 * ncl * 9,
+    HIP_TRY(hipMemcpyAsync(dev + up.tab, tab + (size_t)(k0 - row0) * ncl * 9,
                            (size_t)(k1 - k0) * ncl * 9 * sizeof(double), hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_set_int((int*)(w + B.ctr), 0, s));
-    return SCF_OK;
+    HIP_TRY(launch_set_int((int*)(dev + up.ctr), 0, s));
+    return k1 == nrows ? staged() : SCF_OK;
   };
 
   const int nch = std::max(1, std::min(kReduceChunks, rows[ncl] > 0 ? (rows[ncl] + ncl - 1) / ncl : 1));
@@ -710,11 +705,11 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     ca.y = (const Rt*)y;
     ca.z = (const Rt*)z;
     ca.m = (const Rt*)m;
-    ca.seg_begin = (const int64_t*)(w + B.seg_begin);
-    ca.seg_end = (const int64_t*)(w + B.seg_end);
-    ca.seg_slot = (const int32_t*)(w + B.seg_slot);
+    ca.seg_begin = (const int64_t*)(dev + up.seg_begin);
+    ca.seg_end = (const int64_t*)(dev + up.seg_end);
+    ca.seg_slot = (const int32_t*)(dev + up.seg_slot);
     ca.n = n;
-    ca.nunits = U;
+    ca.nunits = (int)U;
     ca.partials = (Rt*)(w + B.L.partials);
     ca.one_row = rpu == 1;
     ForceArgs<Rt> fa;
@@ -735,9 +730,9 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     fa.n = n;
     fa.image = use_image(p, n / ncl);
     fa.host = hp;
-    fa.blk_cluster = (const int32_t*)(w + B.blk_cluster);
-    fa.blk_begin = (const int64_t*)(w + B.blk_begin);
-    fa.blk_end = (const int64_t*)(w + B.blk_end);
+    fa.blk_cluster = (const int32_t*)(dev + up.blk_cluster);
+    fa.blk_begin = (const int64_t*)(dev + up.blk_begin);
+    fa.blk_end = (const int64_t*)(dev + up.blk_end);
     fa.centre_tab = (const double*)(w + B.cur);
     fa.W_stride = W_stride;
     // one step's kernels: coefficients of every cluster, their reduction and
@@ -747,21 +742,21 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
                        bool store_acc) -> scf_status {
       {
         Timed t(p, q, K_BATCH_COEF);
-        HIP_TRY(p->eng->launch_coef(&ca, U, v, q));
+        HIP_TRY(p->eng->launch_coef(&ca, (int)U, v, q));
       }
       {
         Timed tr(p, q, K_REDUCE);
         const void* part = ca.partials;
         if (!one_pass) {
-          HIP_TRY(launch_reduce_batched(p->dtype, ca.partials, (const int32_t*)(w + B.rows), ncl,
+          HIP_TRY(launch_reduce_batched(p->dtype, ca.partials, (const int32_t*)(dev + up.rows), ncl,
                                         (int)p->T, nch, (double*)(w + B.L.red1), q));
           part = w + B.L.red1;
         }
         HIP_TRY(launch_reduce_final_batched(
-            p->dtype, !one_pass, part, (const int32_t*)(w + B.rows), nch,
+            p->dtype, !one_pass, part, (const int32_t*)(dev + up.rows), nch,
             one_pass ? max_cluster_rows : nch, ncl, weight_tables(p, use_image(p, n / ncl)), coef, Wb,
             W_stride,
-            (const double*)(w + B.tab), (double*)(w + B.cur), (int*)(w + B.ctr), q));
+            (const double*)(dev + up.tab), (double*)(w + B.cur), (int*)(dev + up.ctr), q));
       }
       ForceArgs<Rt> f2 = fa;
       f2.kick = Rt(kick);
@@ -773,9 +768,8 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
       }
       return SCF_OK;
     };
-    scf_status st = upload_rows(acc_valid ? 1 : 0);
-    if (st != SCF_OK) return st;
-    int64_t chunk0 = acc_valid ? 1 : 0;
+    scf_status st = SCF_OK;
+    int64_t chunk0 = row0;
     if (!acc_valid) {
       // a(x0): field pass with no kick and no drift (v is rewritten unchanged)
       st = enqueue(s, 0.0, 0.0, nsteps == 0 && coef_last ? coef_last : coef_int, true);
@@ -798,6 +792,8 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
       add(&dt, sizeof(dt));
       add(&U, sizeof(U));
       add(&nblk, sizeof(nblk));
+      add(&ncl, sizeof(ncl));
+      add(&max_cluster_rows, sizeof(max_cluster_rows));
       add(&nch, sizeof(nch));
       add(&one_pass, sizeof(one_pass));
       add(&v, sizeof(v));
@@ -874,8 +870,7 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     return SCF_OK;
   };
   scf_status st = p->dtype == SCF_F32 ? go(float(0)) : go(double(0));
-  HIP_TRY(hipEventRecord(p->ev_staging, s));
-  p->staging_pending = true;
+  if (st != SCF_OK && !p->staging_pending) (void)staged();
   if (st == SCF_OK) std::copy(cnew.begin(), cnew.end(), centres);
   return st;
 }

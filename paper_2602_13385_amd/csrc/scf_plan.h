@@ -219,10 +219,8 @@ struct scf_plan {
   hipGraphExec_t gexec_g = nullptr;
   std::vector<char> gkey;
   int graph_captures = 0;
-  double* h_tab = nullptr;
-  size_t h_tab_cap = 0;
-  char* h_meta = nullptr;
-  size_t h_meta_cap = 0;
+  char* h_stage = nullptr;
+  size_t h_stage_cap = 0;
   hipEvent_t ev_staging = nullptr;
   bool staging_pending = false;
 };
@@ -336,14 +334,40 @@ WsLayout ws_layout(const scf_plan* p, int64_t n, int nclusters, int nblocks) {
 
 size_t plain_need(const scf_plan* p, int64_t n) { return ws_layout(p, n, 1, 0).total; }
 
-// Batched workspace: the common layout for nclusters, then the centre-table
-// chunk, the current centre rows and step counter, and the work lists.
+// Batched workspace: the common layout for nclusters, then the current centre
+// rows and the region one copy fills at the start of a call: the step counter,
+// the work lists and the first chunk of the centre table (BatchUpload).
 constexpr int kCentreRows = 256;  // centre-table rows uploaded per chunk
 constexpr int kGraphSteps = 8;    // middle steps replayed per graph launch
 
+// Offsets of a call's upload: the step counter (zero), particle ranges and
+// slots of U wave-units, partial-row ranges of the clusters, cluster and
+// particle range of nblk field blocks, and `crows` centre-table rows.
+struct BatchUpload {
+  size_t ctr, seg_begin, seg_end, seg_slot, rows, blk_cluster, blk_begin, blk_end, tab, total;
+  BatchUpload(int64_t U, int ncl, int64_t nblk, int64_t crows) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = off;
+      off += align256(bytes);
+      return at;
+    };
+    ctr = take(sizeof(int));
+    seg_begin = take((size_t)U * 8);
+    seg_end = take((size_t)U * 8);
+    seg_slot = take((size_t)U * 4);
+    rows = take((size_t)(ncl + 1) * 4);
+    blk_cluster = take((size_t)nblk * 4);
+    blk_begin = take((size_t)nblk * 8);
+    blk_end = take((size_t)nblk * 8);
+    tab = take((size_t)crows * ncl * 9 * sizeof(double));
+    total = off;
+  }
+};
+
 struct BatchLayout {
   WsLayout L;
-  size_t tab, cur, ctr, seg_begin, seg_end, seg_slot, rows, blk_cluster, blk_begin, blk_end, total;
+  size_t cur, up, total;
   int max_units;
   int64_t max_blocks;
 };
@@ -360,26 +384,10 @@ BatchLayout batch_layout(const scf_plan* p, int64_t n, int ncl) {
   B.max_blocks = (n + 255) / 256 + ncl;
   B.L = ws_layout(p, n, ncl, max_rows);
   size_t off = B.L.total;
-  B.tab = off;
-  off += align256((size_t)kCentreRows * ncl * 9 * sizeof(double));
   B.cur = off;
   off += align256((size_t)ncl * 9 * sizeof(double));
-  B.ctr = off;
-  off += 256;
-  B.seg_begin = off;
-  off += align256((size_t)max_units * 8);
-  B.seg_end = off;
-  off += align256((size_t)max_units * 8);
-  B.seg_slot = off;
-  off += align256((size_t)max_units * 4);
-  B.rows = off;
-  off += align256((size_t)(ncl + 1) * 4);
-  B.blk_cluster = off;
-  off += align256((size_t)B.max_blocks * 4);
-  B.blk_begin = off;
-  off += align256((size_t)B.max_blocks * 8);
-  B.blk_end = off;
-  off += align256((size_t)B.max_blocks * 8);
+  B.up = off;
+  off += BatchUpload(max_units, ncl, B.max_blocks, kCentreRows).total;
   B.total = off;
   return B;
 }

@@ -274,17 +274,17 @@ hipError_t launch_reduce(int dtype, const void* partials, int nblocks, int T, in
   return hipGetLastError();
 }
 
-// Threads per block, input and real type of a reduction: 256 threads (16 row
-// groups) up to kFewRows partial rows, where the rest of 1024 would have no row
-// to add and the batched step has many such blocks; with 90 rows the larger
-// block is already the faster one (coefficients and reduction of 1e4 points,
-// nmax 6, lmax 4: 8.6 against 9.6 us).
-constexpr int kFewRows = 32;
+// Threads per block, input and real type of a reduction.  256 threads (16 row
+// groups) up to 32 partial rows, where the rest of 1024 would have no row to
+// add, and up to 128 rows when there are blocks enough to fill the chip several
+// times (many clusters); with 90 rows and 25 blocks the larger block is already
+// the faster one (coefficients and reduction of 1e4 points, nmax 6, lmax 4: 8.6
+// against 9.6 us).
 template <typename F>
-static void with_reduce_types(int dtype, bool chunks_f64, int rows, F f) {
+static void with_reduce_types(int dtype, bool chunks_f64, int rows, int blocks, F f) {
   using T4 = std::integral_constant<int, 256>;
   using T16 = std::integral_constant<int, 1024>;
-  const bool few = rows <= kFewRows;
+  const bool few = rows <= (blocks >= 1024 ? 128 : 32);
   if (dtype == 0 && !chunks_f64)
     few ? f(T4{}, float(0), float(0)) : f(T16{}, float(0), float(0));
   else if (dtype == 0)
@@ -297,7 +297,7 @@ hipError_t launch_reduce_final(int dtype, bool chunks_f64, const void* partials,
                                const WeightTables& wt, double* coef, void* W, void* FW,
                                hipStream_t s) {
   const int grid = grid_rows((wt.lmax + 1) * (wt.lmax + 1));
-  with_reduce_types(dtype, chunks_f64, nrows, [&](auto nt, auto in, auto r) {
+  with_reduce_types(dtype, chunks_f64, nrows, grid, [&](auto nt, auto in, auto r) {
     using IN = decltype(in);
     using R = decltype(r);
     constexpr int NT = decltype(nt)::value;
@@ -372,7 +372,7 @@ hipError_t launch_reduce_final_batched(int dtype, bool chunks_f64, const void* p
   if (ncl <= 0) return hipSuccess;
   const dim3 grid(grid_rows((wt.lmax + 1) * (wt.lmax + 1)), ncl);
   const int nch = chunks_f64 ? nchunks : 0;
-  with_reduce_types(dtype, chunks_f64, max_rows, [&](auto nt, auto in, auto r) {
+  with_reduce_types(dtype, chunks_f64, max_rows, (int)(grid.x * grid.y), [&](auto nt, auto in, auto r) {
     using IN = decltype(in);
     using R = decltype(r);
     constexpr int NT = decltype(nt)::value;
