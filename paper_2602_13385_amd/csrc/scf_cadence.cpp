@@ -86,34 +86,58 @@ scf_status frozen_steps(scf_plan* p, int64_t n, void* x, void* y, void* z, void*
     }
   };
   double row[6];
-  scf_status st;
-  if (!acc_valid || nsteps == 0) {
+  if (nsteps == 0) {
     cen_row(row);
-    st = run_field<R>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, W, hp, row, 0, 0.0, 0.0, s);
-    if (st != SCF_OK) return st;
+    return run_field<R>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, W, hp, row, 0, 0.0, 0.0, s);
   }
-  if (nsteps == 0) return SCF_OK;
+  // Evaluations at the substeps' positions, kRunEvals to a launch: at x0 too
+  // when there are no stored accelerations (half kick, drift), then at every
+  // substep's end, where the closing half kick of a substep is merged with the
+  // opening one of the next.  The accelerations of the last one are stored.
   const double h = 0.5 * dt;
-  {
-    Timed t(p, s, K_KICK);
-    HIP_TRY(launch_kick_drift(p->dtype, n, x, y, z, vx, vy, vz, ax, ay, az, h, dt, s));
-  }
-  double gc[3];
-  centre_accel(hd, Rc, gc);
-  for (int i = 0; i < 3; ++i) Vc[i] += h * gc[i];
-  for (int i = 0; i < 3; ++i) Rc[i] += dt * Vc[i];
-  for (int k = 1; k <= nsteps; ++k) {
-    const bool last = k == nsteps;
-    cen_row(row);
-    // closing half kick of step k merged with the opening half kick of step
-    // k+1, then the drift of step k+1; a at the new positions into ax, ay, az
-    st = run_field<R>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, W, hp, row, 1, last ? h : dt,
-                      last ? 0.0 : dt, s);
-    if (st != SCF_OK) return st;
+  RunArgs<R> ra;
+  fill_force_common(ra.f, p);
+  ra.f.x = (R*)x;
+  ra.f.y = (R*)y;
+  ra.f.z = (R*)z;
+  ra.f.vx = (R*)vx;
+  ra.f.vy = (R*)vy;
+  ra.f.vz = (R*)vz;
+  ra.f.W = (const R*)W;
+  ra.f.n = n;
+  ra.f.image = use_image(p, n);
+  ra.f.host = hp;
+  ra.nev = 0;
+  ra.open = acc_valid ? 1 : 0;
+  ra.open_kick = R(h);
+  ra.open_drift = R(dt);
+  auto move_centre = [&](double kick, double drift) {
+    double gc[3];
     centre_accel(hd, Rc, gc);
-    for (int i = 0; i < 3; ++i) Vc[i] += (last ? h : dt) * gc[i];
-    if (!last)
-      for (int i = 0; i < 3; ++i) Rc[i] += dt * Vc[i];
+    for (int i = 0; i < 3; ++i) Vc[i] += kick * gc[i];
+    if (drift != 0.0)
+      for (int i = 0; i < 3; ++i) Rc[i] += drift * Vc[i];
+  };
+  if (acc_valid) move_centre(h, dt);
+  for (int k = acc_valid ? 1 : 0; k <= nsteps; ++k) {
+    const bool last = k == nsteps;
+    const double kick = k == 0 || last ? h : dt, drift = last ? 0.0 : dt;
+    cen_row(row);
+    R* r = ra.row[ra.nev++];
+    for (int i = 0; i < 6; ++i) r[i] = R(row[i]);
+    r[6] = R(kick);
+    r[7] = R(drift);
+    move_centre(kick, drift);
+    if (!last && ra.nev < kRunEvals) continue;
+    ra.f.ax = ra.open || last ? (R*)ax : nullptr;
+    ra.f.ay = ra.open || last ? (R*)ay : nullptr;
+    ra.f.az = ra.open || last ? (R*)az : nullptr;
+    if (n > 0) {
+      Timed t(p, s, K_STEP_FIELD);
+      HIP_TRY(p->eng->launch_run(&ra, (n + 255) / 256, p->field_variant, s));
+    }
+    ra.nev = 0;
+    ra.open = 0;
   }
   return SCF_OK;
 }

@@ -130,6 +130,20 @@ struct ForceArgs {
   const double* dtab;
 };
 
+// A run of field evaluations in a frozen potential, each followed by a kick and
+// a drift: row e holds the centre R and grad psi_host(R) of evaluation e, its
+// kick and its drift (0: none).  open: the stored accelerations' kick and drift
+// come first.  The accelerations of the last evaluation go to f.ax, f.ay, f.az
+// (nullable).
+constexpr int kRunEvals = 32;
+template <typename R>
+struct RunArgs {
+  ForceArgs<R> f;
+  int nev, open;
+  R open_kick, open_drift;
+  R row[kRunEvals][8];
+};
+
 // Kernel arguments of the adjoint's Hessian-vector kernel (T = float or double).
 template <typename T>
 struct HvpArgs {
@@ -179,6 +193,9 @@ struct Engine {
   virtual int field_variants() const = 0;
   virtual hipError_t launch_force(const void* args, int64_t nblocks, int mode, int fv,
                                   hipStream_t s) const = 0;
+  // launches a run (RunArgs) over nblocks blocks of 256 particles
+  virtual hipError_t launch_run(const void* args, int64_t nblocks, int fv,
+                                hipStream_t s) const = 0;
   // adjoint: the gamma pass (coefficient kernel on dual positions, one
   // variant) and the Hessian-vector kernel
   virtual int gamma_stage_particles() const = 0;

@@ -1310,6 +1310,208 @@ field_image_kernel(ForceArgs<float> a) {
   field_image_body<NMAXC, LMAX, MODE, BATCHED>(a);
 }
 
+// ---------------------------------------------------------------------------
+// runs in a frozen potential
+// ---------------------------------------------------------------------------
+// With the weights fixed, a particle's substeps do not depend on the other
+// particles, so one launch takes up to kRunEvals of them with the state in
+// registers: no launch, no kernel tail and no load of the weights into cold
+// caches per substep (interval of 159 substeps, 1e5 particles, nmax 10, lmax 6:
+// see the launch sequence, frozen_steps).  Same arithmetic as the one-substep
+// kernels, variant by variant.
+template <typename R>
+struct RunState {
+  R x, y, z, vx, vy, vz, ax, ay, az;
+};
+template <typename R>
+__device__ __forceinline__ RunState<R> run_load(const RunArgs<R>& a, const int64_t i) {
+  const ForceArgs<R>& f = a.f;
+  RunState<R> q;
+  q.x = f.x[i];
+  q.y = f.y[i];
+  q.z = f.z[i];
+  q.vx = f.vx[i];
+  q.vy = f.vy[i];
+  q.vz = f.vz[i];
+  q.ax = q.ay = q.az = R(0);
+  if (a.open) {
+    q.vx = fma(a.open_kick, f.ax[i], q.vx);
+    q.vy = fma(a.open_kick, f.ay[i], q.vy);
+    q.vz = fma(a.open_kick, f.az[i], q.vz);
+    q.x = fma(a.open_drift, q.vx, q.x);
+    q.y = fma(a.open_drift, q.vy, q.y);
+    q.z = fma(a.open_drift, q.vz, q.z);
+  }
+  return q;
+}
+// kick and drift of evaluation e from the SCF acceleration in q.ax, q.ay, q.az
+template <typename R>
+__device__ __forceinline__ void run_kick(const RunArgs<R>& a, const int e, RunState<R>& q) {
+  const R* __restrict__ r = a.row[e];
+  if (a.f.host.ncomp > 0) {
+    R hx, hy, hz;
+    host_grad<R>(a.f.host, r[0] + q.x, r[1] + q.y, r[2] + q.z, hx, hy, hz);
+    q.ax += r[3] - hx;
+    q.ay += r[4] - hy;
+    q.az += r[5] - hz;
+  }
+  q.vx = fma(r[6], q.ax, q.vx);
+  q.vy = fma(r[6], q.ay, q.vy);
+  q.vz = fma(r[6], q.az, q.vz);
+  if (r[7] != R(0)) {
+    q.x = fma(r[7], q.vx, q.x);
+    q.y = fma(r[7], q.vy, q.y);
+    q.z = fma(r[7], q.vz, q.z);
+  }
+}
+template <typename R>
+__device__ __forceinline__ void run_store(const RunArgs<R>& a, const int64_t i,
+                                          const RunState<R>& q) {
+  const ForceArgs<R>& f = a.f;
+  f.x[i] = q.x;
+  f.y[i] = q.y;
+  f.z[i] = q.z;
+  f.vx[i] = q.vx;
+  f.vy[i] = q.vy;
+  f.vz[i] = q.vz;
+  if (f.ax) {
+    f.ax[i] = q.ax;
+    f.ay[i] = q.ay;
+    f.az[i] = q.az;
+  }
+}
+
+// field variants 0 and 1 (one particle per thread)
+template <typename R, int NMAXC, int LMAX>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2)))
+field_run_kernel(RunArgs<R> a) {
+  const ForceArgs<R>& f = a.f;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const uint32_t tw =
+      touch_lines(f.W, (LMAX + 1) * (LMAX + 1) * (NMAXC + 1) * (int)sizeof(R));
+  if (i >= f.n) return;
+  RunState<R> q = run_load(a, i);
+#pragma unroll 1
+  for (int e = 0; e < a.nev; ++e) {
+    R psi;
+    field_eval<R, NMAXC, LMAX>(q.x, q.y, q.z, f.W, f.beta_rad, f.beta_ang, f.binv, f.alpha,
+                               f.inv_alpha, f.amode, psi, q.ax, q.ay, q.az);
+    run_kick(a, e, q);
+  }
+  run_store(a, i, q);
+  touch_done(tw);
+}
+
+// the split-degree variants (S parts per particle): part 0 holds the velocity
+// and hands the drifted position to the others
+template <typename R, int NMAXC, int LMAX, int S>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 2)))
+field_run_split(RunArgs<R> a) {
+  constexpr int P = 256 / S;
+  constexpr DegreeSplit<LMAX, S> sp{};
+  __shared__ R part[S - 1][5][P];
+  __shared__ R pos[3][P];
+  const ForceArgs<R>& f = a.f;
+  const int t = threadIdx.x % P;
+  const int h = __builtin_amdgcn_readfirstlane(threadIdx.x / P);
+  const int64_t i0 = (int64_t)blockIdx.x * P + t;
+  const bool live = i0 < f.n;
+  const int64_t i = live ? i0 : f.n - 1;  // every thread reaches the barriers
+  const uint32_t tw =
+      touch_lines(f.W, (LMAX + 1) * (LMAX + 1) * (NMAXC + 1) * (int)sizeof(R));
+  RunState<R> q = run_load(a, i);
+  int lo = sp.begin[0], hi = sp.begin[1] - 1;
+#pragma unroll
+  for (int k = 1; k < S; ++k)
+    if (h == k) {
+      lo = sp.begin[k];
+      hi = sp.begin[k + 1] - 1;
+    }
+#pragma unroll 1
+  for (int e = 0; e < a.nev; ++e) {
+    const Geom<R> g = make_geom<R>(q.x, q.y, q.z, R(f.binv), R(f.alpha), R(f.inv_alpha), f.amode);
+    R psi, psir, gx, gy, gz;
+    field_sums<R, NMAXC, LMAX, true>(g, f.W, f.beta_rad, f.beta_ang, lo, hi, psi, psir, gx, gy, gz);
+    if (h) {
+      part[h - 1][0][t] = psi;
+      part[h - 1][1][t] = psir;
+      part[h - 1][2][t] = gx;
+      part[h - 1][3][t] = gy;
+      part[h - 1][4][t] = gz;
+    }
+    __syncthreads();
+    if (!h) {
+#pragma unroll
+      for (int k = 0; k < S - 1; ++k) {
+        psi += part[k][0][t];
+        psir += part[k][1][t];
+        gx += part[k][2][t];
+        gy += part[k][3][t];
+        gz += part[k][4][t];
+      }
+      field_cartesian<R>(g, psir, gx, gy, gz, q.ax, q.ay, q.az);
+      run_kick(a, e, q);
+      pos[0][t] = q.x;
+      pos[1][t] = q.y;
+      pos[2][t] = q.z;
+    }
+    __syncthreads();
+    q.x = pos[0][t];
+    q.y = pos[1][t];
+    q.z = pos[2][t];
+  }
+  if (!h && live) run_store(a, i, q);
+  touch_done(tw);
+}
+
+// the matrix-core variants: operands built in LDS, or read from the image
+template <int NMAXC, int LMAX>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+field_run_mfma(RunArgs<float> a) {
+  using S = MfmaShape<NMAXC, LMAX>;
+  __shared__ __align__(16) float img[S::IMG];
+  __shared__ float tab[S::TAB];
+  const ForceArgs<float>& f = a.f;
+  build_mfma_operands_call<NMAXC, LMAX>(img, tab, f.W, f.dtab, f.beta_rad);
+  __syncthreads();
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool live = i < f.n;
+  RunState<float> q = run_load(a, live ? i : f.n - 1);
+#pragma unroll 1
+  for (int e = 0; e < a.nev; ++e) {
+    float psi;
+    field_eval_mfma<NMAXC, LMAX>(q.x, q.y, q.z, img, tab, f.binv, f.alpha, f.inv_alpha, f.amode,
+                                 psi, q.ax, q.ay, q.az);
+    run_kick(a, e, q);
+  }
+  if (live) run_store(a, i, q);
+}
+template <int NMAXC, int LMAX>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+field_run_image(RunArgs<float> a) {
+  const ForceArgs<float>& f = a.f;
+  const float* __restrict__ img0 = f.W + FwLayout::img0(NMAXC, LMAX);
+  const uint32_t tw = touch_lines(img0, FwLayout::off(LMAX + 1, NMAXC) * 256);
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool live = i < f.n;
+  RunState<float> q = run_load(a, live ? i : f.n - 1);
+  int lane = threadIdx.x & 63;
+#pragma unroll 1
+  for (int e = 0; e < a.nev; ++e) {
+    // (the operands are read anew in each evaluation: held across the loop
+    // they would fill the registers)
+    asm("" : "+v"(lane));
+    const Geom<float> g =
+        make_geom<float>(q.x, q.y, q.z, f.binv, f.alpha, f.inv_alpha, f.amode);
+    float psi, psir, gx, gy, gz;
+    field_sums_image<NMAXC, LMAX>(g, img0 + lane, f.beta_img, psi, psir, gx, gy, gz);
+    field_cartesian<float>(g, psir, gx, gy, gz, q.ax, q.ay, q.az);
+    run_kick(a, e, q);
+  }
+  if (live) run_store(a, i, q);
+  touch_done(tw);
+}
+
 // sum over the 64 lanes of a wave (every lane receives the total)
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -2037,6 +2239,28 @@ struct EngineImpl final : Engine {
       else
         field_kernel<R, NMAXC, LMAX, 2, false><<<g, 256, 0, s>>>(fa);
     }
+    return hipGetLastError();
+  }
+  hipError_t launch_run(const void* args, int64_t nblocks, int fv, hipStream_t s) const override {
+    if (nblocks <= 0) return hipSuccess;
+    const RunArgs<R>& ra = *(const RunArgs<R>*)args;
+    const dim3 g((unsigned)nblocks);
+    if constexpr (sizeof(R) == 4) {
+      if (fv == 2 || fv == 3) {
+        if (ra.f.image)
+          field_run_image<NMAXC, LMAX><<<g, 256, 0, s>>>(ra);
+        else
+          field_run_mfma<NMAXC, LMAX><<<g, 256, 0, s>>>(ra);
+        return hipGetLastError();
+      }
+    }
+    if (fv == kSplitVariant)
+      field_run_split<R, NMAXC, LMAX, 2>
+          <<<dim3((unsigned)((ra.f.n + 127) / 128)), 256, 0, s>>>(ra);
+    else if (fv > kSplitVariant)
+      field_run_split<R, NMAXC, LMAX, 4><<<dim3((unsigned)((ra.f.n + 63) / 64)), 256, 0, s>>>(ra);
+    else
+      field_run_kernel<R, NMAXC, LMAX><<<g, 256, 0, s>>>(ra);
     return hipGetLastError();
   }
   // adjoint gamma pass: variant 0's lane split on dual numbers
