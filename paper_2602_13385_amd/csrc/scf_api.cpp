@@ -1013,6 +1013,8 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
         ha.W = (const Rt*)Wk(k);
         ha.beta_rad = (const Rt*)p->d_beta_rad;
         ha.beta_ang = (const Rt*)p->d_beta_ang;
+        ha.beta_img = (const Rt*)p->d_beta_img;
+        ha.image = use_image(p, n);
         ha.n = n;
         ha.binv = Rt(1.0 / p->basis.b);
         ha.alpha = Rt(p->basis.alpha);

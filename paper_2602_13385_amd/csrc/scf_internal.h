@@ -160,6 +160,8 @@ struct HvpArgs {
   const T* W;  // field weights of the coefficients at x
   const T* beta_rad;
   const T* beta_ang;
+  const T* beta_img;  // as in ForceArgs
+  int image;
   int64_t n;
   T binv, alpha, inv_alpha;
   int amode;

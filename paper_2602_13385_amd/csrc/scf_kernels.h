@@ -1264,6 +1264,121 @@ __device__ __forceinline__ void field_sums_image(const Geom<float>& g,
   psir = fmaf(g.ir, rr, psir);
 }
 
+// The same sums on dual numbers, for the adjoint's Hessian-vector product: the
+// derivative part of a sum over p_n is the same sum over the derivative parts
+// of p_n, so every chain of matrix-core products runs twice, on the values and
+// on the derivatives.  psi itself is not formed.
+template <int NMAXC, int LMAX>
+__device__ __forceinline__ void field_sums_image_dual(const Geom<Dual<float>>& g,
+                                                      const float* __restrict__ img,
+                                                      const float* __restrict__ bF,
+                                                      Dual<float>& psir, Dual<float>& gx,
+                                                      Dual<float>& gy, Dual<float>& gz) {
+  using D = Dual<float>;
+  constexpr int L1 = LMAX + 1, NP = NMAXC + 2;
+  D Gl = g.g0;
+  D QA[L1], QB[L1], PC[L1], PS[L1], RC[L1], RS[L1], ZC[L1], ZS[L1];
+  QA[0] = D(1.f);
+  static_for<0, L1>([&](auto lc) {
+    constexpr int l = decltype(lc)::value;
+    D(&QW)[L1] = (l & 1) ? QB : QA;
+    const D(&QR)[L1] = (l & 1) ? QA : QB;
+    const float* __restrict__ src = img + FwLayout::off(l, NMAXC) * 64;
+    const float* __restrict__ b = bF + l * NP;
+    if constexpr (l > 0) Gl = Gl * g.w;
+    D p[NP];
+    p[0] = Gl;
+    p[1] = g.xi * Gl;
+#pragma unroll
+    for (int n = 2; n < NP; ++n) p[n] = g.xi * p[n - 1] - b[n] * p[n - 2];
+    D Qup = D(0.f);
+    static_for_down<l, 1>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      constexpr int vlo = (m * NP) >> 4, vhi = (m * NP + NP - 1) >> 4;
+      float cw[vhi - vlo + 1];
+#pragma unroll
+      for (int v = vlo; v <= vhi; ++v) cw[v - vlo] = src[v * 64];
+      mfma_f4 av = {0.f, 0.f, 0.f, 0.f}, ad = {0.f, 0.f, 0.f, 0.f};
+      static_for<0, NP>([&](auto nc) {
+        constexpr int n = decltype(nc)::value;
+        constexpr int q = m * NP + n;
+        av = mfma_bcast<q>(cw[(q >> 4) - vlo], p[n].v, av);
+        ad = mfma_bcast<q>(cw[(q >> 4) - vlo], p[n].d, ad);
+      });
+      const D sc(av[0], ad[0]), rc(av[1], ad[1]), ss(av[2], ad[2]), rs(av[3], ad[3]);
+      D Q;
+      if constexpr (l == m)
+        Q = D(1.f);
+      else if constexpr (l == m + 1)
+        Q = g.c;
+      else
+        Q = g.c * QR[m] - float(legendre_b(l, m)) * QW[m];
+      QW[m] = Q;
+      const D dQ = float(l - m) * Qup;
+      Qup = Q;
+      if constexpr (l == 0) {
+        psir = g.dxi * rc - g.kap * sc;
+        PC[0] = RC[0] = ZC[0] = D(0.f);
+      } else if constexpr (l == m) {
+        PC[m] = sc;
+        RC[m] = rc;
+        PS[m] = ss;
+        RS[m] = rs;
+      } else {
+        if constexpr (m > 0) PC[m] = fma(Q, sc, PC[m]);  // (order 0's potential is not needed)
+        RC[m] = fma(Q, rc, RC[m]);
+        if constexpr (m == 0) {
+          ZC[m] = fma(dQ, sc, ZC[m]);
+        } else {
+          PS[m] = fma(Q, ss, PS[m]);
+          RS[m] = fma(Q, rs, RS[m]);
+          if constexpr (l == m + 1) {
+            ZC[m] = dQ * sc;
+            ZS[m] = dQ * ss;
+          } else {
+            ZC[m] = fma(dQ, sc, ZC[m]);
+            ZS[m] = fma(dQ, ss, ZS[m]);
+          }
+        }
+      }
+      // (the sums are due here, as in field_sums_image)
+      asm("" : "+v"(RC[m].v), "+v"(RC[m].d));
+      if constexpr (m > 0) {
+        asm("" : "+v"(PC[m].v), "+v"(PC[m].d), "+v"(PS[m].v), "+v"(PS[m].d));
+        asm("" : "+v"(RS[m].v), "+v"(RS[m].d));
+      }
+      if constexpr (l > m) {
+        asm("" : "+v"(ZC[m].v), "+v"(ZC[m].d));
+        if constexpr (m > 0) asm("" : "+v"(ZS[m].v), "+v"(ZS[m].d));
+      }
+    });
+  });
+  D rr = RC[0];
+  gx = D(0.f);
+  gy = D(0.f);
+  gz = ZC[0];
+  D er = D(1.f), ei = D(0.f);  // E_{m-1}
+  static_for<1, L1>([&](auto mc) {
+    constexpr int m = decltype(mc)::value;
+    const D c = float(m) * PC[m], s = float(m) * PS[m];
+    if constexpr (m == 1) {
+      gx = c;
+      gy = s;
+      er = g.ux;
+      ei = g.uy;
+    } else {
+      gx = fma(c, er, fma(s, ei, gx));
+      gy = fma(s, er, gy) - c * ei;
+      const D nr = er * g.ux - ei * g.uy;
+      ei = er * g.uy + ei * g.ux;
+      er = nr;
+    }
+    rr = fma(RC[m], er, fma(RS[m], ei, rr));
+    if constexpr (m < LMAX) gz = fma(ZC[m], er, fma(ZS[m], ei, gz));
+  });
+  psir = fma(g.ir, rr, psir);
+}
+
 // Body of the kernel: a wave evaluates 64 particles by itself; lanes past the
 // end evaluate the last particle (so that every lane joins the MFMAs) and store
 // nothing.  In batched mode every block lies inside one cluster, whose image it
@@ -1529,7 +1644,9 @@ __device__ __forceinline__ T wave_sum(T v) {
 // block also writes the sums over its particles of -Hess psi_host(R + x_i) mu_i
 // (3), mu_i (3) and -mu_i . d grad psi_host(R + x_i) / d p_ck (3 per
 // component) to partials[block][0..31], in the order listed.
-template <typename T, int NMAXC, int LMAX>
+// IMAGE (single precision): the sums on the matrix cores from the operand image
+// (use_image); at 1e5 particles, nmax 10, lmax 6, 19.9 us against 26.6.
+template <typename T, int NMAXC, int LMAX, bool IMAGE>
 __global__ void __launch_bounds__(256) hvp_kernel(HvpArgs<T> a) {
   using D = Dual<T>;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1540,8 +1657,17 @@ __global__ void __launch_bounds__(256) hvp_kernel(HvpArgs<T> a) {
   T my = valid ? a.c * a.lvy[ii] : T(0);
   T mz = valid ? a.c * a.lvz[ii] : T(0);
   D psi, ax, ay, az;
-  field_eval<D, NMAXC, LMAX>(D(x, mx), D(y, my), D(z, mz), a.W, a.beta_rad, a.beta_ang, a.binv,
-                             a.alpha, a.inv_alpha, a.amode, psi, ax, ay, az);
+  if constexpr (IMAGE) {
+    const Geom<D> g = make_geom<D>(D(x, mx), D(y, my), D(z, mz), D(a.binv), D(a.alpha),
+                                   D(a.inv_alpha), a.amode);
+    D psir, gx, gy, gz;
+    field_sums_image_dual<NMAXC, LMAX>(
+        g, a.W + FwLayout::img0(NMAXC, LMAX) + (threadIdx.x & 63), a.beta_img, psir, gx, gy, gz);
+    field_cartesian<D>(g, psir, gx, gy, gz, ax, ay, az);
+  } else {
+    field_eval<D, NMAXC, LMAX>(D(x, mx), D(y, my), D(z, mz), a.W, a.beta_rad, a.beta_ang, a.binv,
+                               a.alpha, a.inv_alpha, a.amode, psi, ax, ay, az);
+  }
   T ox = ax.d, oy = ay.d, oz = az.d;
   if (a.host.ncomp > 0) {
     __shared__ T red[4][32];
@@ -1569,9 +1695,13 @@ __global__ void __launch_bounds__(256) hvp_kernel(HvpArgs<T> a) {
             v[6 + 3 * c + k] = -host_dgrad_dparam_dot<T>(a.host, c, k, px, py, pz, mx, my, mz);
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // (the sums past the host's parameters are zero: their 6 lane exchanges
+    // each are skipped)
+    const int nq = 6 + 3 * a.host.ncomp;
 #pragma unroll
     for (int q = 0; q < 32; ++q) {
-      const T t = wave_sum(v[q]);
+      T t = T(0);
+      if (q < nq) t = wave_sum(v[q]);
       if (lane == q) red[wave][q] = t;
     }
     __syncthreads();
@@ -2285,7 +2415,13 @@ struct EngineImpl final : Engine {
   hipError_t launch_hvp(const void* args, int64_t nblocks, hipStream_t s) const override {
     if (nblocks <= 0) return hipSuccess;
     const HvpArgs<R>& ha = *(const HvpArgs<R>*)args;
-    hvp_kernel<R, NMAXC, LMAX><<<dim3((unsigned)nblocks), 256, 0, s>>>(ha);
+    if constexpr (sizeof(R) == 4) {
+      if (ha.image) {
+        hvp_kernel<R, NMAXC, LMAX, true><<<dim3((unsigned)nblocks), 256, 0, s>>>(ha);
+        return hipGetLastError();
+      }
+    }
+    hvp_kernel<R, NMAXC, LMAX, false><<<dim3((unsigned)nblocks), 256, 0, s>>>(ha);
     return hipGetLastError();
   }
   const char* describe() const override {
