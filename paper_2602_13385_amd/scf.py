@@ -245,18 +245,25 @@ def make_host(components, G=1.0):
     return h
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
+    # (the raw handle: building a Stream object for it takes 3 us a call)
     torch = _torch()
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def tidal_norm(host, pos):
@@ -280,6 +287,7 @@ class Plan:
         _check(lib().scf_plan_create(C.byref(self._h), C.byref(self.basis), self.dtype, 0))
         self.T = ncoef(self.nmax, self.lmax)
         self._ws = None
+        self._need = (None, 0)  # workspace bytes of the last (n, nclusters) asked for
 
     @property
     def torch_dtype(self):
@@ -358,18 +366,23 @@ class Plan:
 
     def workspace(self, n, nclusters=1, device=None):
         torch = _torch()
-        need = C.c_size_t()
-        _check(lib().scf_workspace_size(self._h, int(n), int(nclusters), C.byref(need)))
-        if self._ws is None or self._ws.numel() < need.value:
-            self._ws = torch.empty(max(need.value, 256), dtype=torch.uint8,
+        key, size = self._need
+        if key != (n, nclusters):
+            need = C.c_size_t()
+            _check(lib().scf_workspace_size(self._h, int(n), int(nclusters), C.byref(need)))
+            size = need.value
+            self._need = ((n, nclusters), size)
+        if self._ws is None or self._ws.numel() < size:
+            self._ws = torch.empty(max(size, 256), dtype=torch.uint8,
                                    device=device or torch.device("cuda"))
         return self._ws
 
     def _check_arrays(self, *ts):
+        dtype = self.torch_dtype
         for t in ts:
             if t is None:
                 continue
-            if t.dtype != self.torch_dtype or not t.is_cuda or not t.is_contiguous():
+            if t.dtype != dtype or not t.is_cuda or not t.is_contiguous():
                 raise TypeError(f"expected contiguous {self.torch_dtype} CUDA tensors")
 
     def coeffs(self, x, y, z, m, out=None):
