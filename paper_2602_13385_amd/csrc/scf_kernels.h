@@ -1929,6 +1929,13 @@ struct BlkShape {
   static constexpr int P = G * PPG;             // particles per stage
   static constexpr int SLOT = NT * NR * JT;   // values of one group's tiles
   static constexpr int NSLOT = (P * PS) / SLOT;  // group tiles the stage buffer holds
+  // groups left when the pairwise sum can finish from the stage buffer at once
+  static constexpr int groups_left() {
+    int a = G;
+    while (a > NSLOT) a = (a + 1) / 2;
+    return a;
+  }
+  static constexpr int AF = groups_left();
   static constexpr int aoff(int l) { return JT * ntiles_c(l - 1, JT); }
   static_assert(G >= 1 && NT * G <= THREADS, "tiles must fit the block");
   static_assert(NSLOT >= 1, "the stage buffer must hold one group's tiles");
@@ -1960,6 +1967,18 @@ __device__ __forceinline__ void load4(const double* p, double (&v)[4]) {
 __device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
 
+// v[0] = the sum of v[0 .. A-1], halving by halving: with h = (a + 1) / 2,
+// v[g] += v[g + h] for g < a - h, then a = h
+template <int A, typename R, int N>
+__device__ __forceinline__ void static_halvings(R (&v)[N]) {
+  if constexpr (A > 1) {
+    constexpr int H = (A + 1) / 2;
+#pragma unroll
+    for (int g = 0; g < A - H; ++g) v[g] += v[g + H];
+    static_halvings<H>(v);
+  }
+}
+
 // Block coefficient kernel.  R = float is the single-precision pass with
 // compensated folds into (hi, lo) rows; R = double (a variant of the
 // double-precision plans) adds its folds into one double row per unit.
@@ -1969,7 +1988,7 @@ __attribute__((amdgpu_waves_per_eu(blk_waves<NMAXC, R>(), blk_waves<NMAXC, R>())
 coef_blk_kernel(CoefArgs<R> a) {
   using S = BlkShape<NMAXC, LMAX, R>;
   constexpr int NR = S::NR, NT = S::NT, G = S::G, P = S::P, PS = S::PS, XI = S::XI;
-  constexpr int PPG = S::PPG, SLOT = S::SLOT, NSLOT = S::NSLOT, L2 = (LMAX + 1) * (LMAX + 1);
+  constexpr int PPG = S::PPG, SLOT = S::SLOT, NSLOT = S::NSLOT, AF = S::AF, L2 = (LMAX + 1) * (LMAX + 1);
   __shared__ __align__(16) R rec[P * PS];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -2109,8 +2128,9 @@ coef_blk_kernel(CoefArgs<R> a) {
     const bool last = base + P >= end;
     if (since == FOLD || last) {
       __syncthreads();  // every group has finished reading the stage
-      // ---- groups summed pairwise into group 0 through the stage buffer ----
-      for (int active = G; active > 1;) {
+      // ---- groups summed pairwise through the stage buffer: in rounds (two
+      // barriers each) until the tiles of the groups left fit it ----
+      for (int active = G; active > AF;) {
         const int half = (active + 1) / 2, movers = active - half;
         for (int c0 = 0; c0 < movers; c0 += NSLOT) {
           const int c1 = movers < c0 + NSLOT ? movers : c0 + NSLOT;
@@ -2137,10 +2157,14 @@ coef_blk_kernel(CoefArgs<R> a) {
         active = half;
       }
       // ---- two-sum fold of the block's sums into the unit's (hi, lo) rows ----
-      // group 0 leaves its tiles in the stage buffer; every thread then folds
-      // coefficients t = tid, tid + 256, .. (coalesced rows)
-      if (tv && grp == 0) {
-        R* d = rec + tau * NR * 4;
+      // the AF groups left leave their tiles in the stage buffer; every thread
+      // then adds the AF values of coefficients e = tid, tid + 256, .. in the
+      // order of the rounds (the same bits) and folds the sum.  With a round
+      // per halving down to one group, a unit of one stage spent as long in
+      // barriers as in its products: nmax 6, lmax 4, 1e4 points (G = 28) 4.0
+      // us against 5.2, nmax 10, lmax 6, 1e5 points (G = 16) 8.3 against 9.7.
+      if (tv && grp < AF) {
+        R* d = rec + grp * SLOT + tau * NR * 4;
 #pragma unroll
         for (int n = 0; n < NR; ++n) store4(d + 4 * n, acc[n][0], acc[n][1], acc[n][2], acc[n][3]);
       }
@@ -2153,7 +2177,12 @@ coef_blk_kernel(CoefArgs<R> a) {
         // column of j in the l-block, and the tile holding it
         const int c = j == 0 ? 0 : j + 1;
         const int tau_t = (l == 0 ? 0 : l + (l - 1) * (l - 1) / 4) + (c >> 2);
-        const R v = rec[(tau_t * NR + n) * 4 + (c & 3)];
+        const R* src = rec + (tau_t * NR + n) * 4 + (c & 3);
+        R vg[AF];
+#pragma unroll
+        for (int g = 0; g < AF; ++g) vg[g] = src[g * SLOT];
+        static_halvings<AF>(vg);
+        const R v = vg[0];
         if (first_fold) {
           hi[t] = v;
           if constexpr (sizeof(R) == 4)
