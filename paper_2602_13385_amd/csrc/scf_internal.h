@@ -201,6 +201,8 @@ struct Engine {
   // adjoint: the gamma pass (coefficient kernel on dual positions, one
   // variant) and the Hessian-vector kernel
   virtual int gamma_stage_particles() const = 0;
+  // stages per fold (0: no folds); units that fold once write one row
+  virtual int gamma_fold_stages() const = 0;
   virtual int gamma_rows_per_unit() const = 0;
   virtual int gamma_resident_units() const = 0;
   virtual hipError_t launch_gamma(const void* args, int nunits, hipStream_t s) const = 0;

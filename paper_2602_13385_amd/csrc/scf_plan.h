@@ -770,11 +770,13 @@ scf_status run_gamma(scf_plan* p, int64_t n, const void* x, const void* y, const
   ca.stages = stages;
   ca.nunits = units;
   ca.partials = (acc_t<Dual<R>>*)(ws + L.partials);
+  const int fold = p->eng->gamma_fold_stages();
+  ca.one_row = fold > 0 && (stages + units - 1) / units <= fold;
   {
     Timed t(p, s, K_ADJ);
     HIP_TRY(p->eng->launch_gamma(&ca, units, s));
   }
-  const int rows = units * p->eng->gamma_rows_per_unit();
+  const int rows = units * (ca.one_row ? 1 : p->eng->gamma_rows_per_unit());
   return reduce_and_finalize(p, ws + L.partials, rows, nullptr, nullptr, Wout, use_image(p, n), ws,
                              L, s);
 }
