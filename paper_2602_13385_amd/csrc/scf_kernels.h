@@ -2025,9 +2025,10 @@ __device__ __forceinline__ void static_halvings(R (&v)[N]) {
 // Dual<float> is the adjoint's gamma pass: the records hold the values and the
 // derivatives of the angular columns and xi, and a tile adds the derivative of
 // each product, 13 multiply-adds per n and column quad where the values alone
-// take 6.  The wave-unit kernel it replaced rebuilt m G_l times the angular
-// columns per lane and kept one wave per SIMD: at 1e5 particles, nmax 10, lmax
-// 6, 18.3 us against 14.3 (20-step gradient 2646 against 2514 us).
+// take 6.  The wave-unit kernel it replaced multiplied m G_l into the columns
+// in every tile and held two waves per SIMD (148 registers; one at nmax 16,
+// lmax 10): at 1e5 particles, nmax 10, lmax 6, 18.3 us against 14.3 (20-step
+// gradient 2646 against 2514 us).
 template <int NMAXC, int LMAX, int FOLD, typename E = float>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(blk_waves<NMAXC, LMAX, E>(), blk_waves<NMAXC, LMAX, E>())))
@@ -2409,11 +2410,13 @@ struct EngineImpl final : Engine {
     return hipGetLastError();
   }
   // field variants: 0 and 1 = VALU kernel under two register budgets; 2 and 3
-  // (single precision) = matrix-core kernel under two register budgets; the
-  // last two (4 and 5 in single, 2 and 3 in double precision) = VALU kernel
-  // with each point's degrees split over 2 or 4 waves.  The batched step runs
-  // variant 1's kernel for variants 1 to 3; the adjoint's accumulation pass
-  // runs variant 0's for variants 0 to 3 and the split kernels for theirs.
+  // (single precision) = matrix cores, from the operand image in every mode where
+  // `image` is set (use_image), else from operands built per block in LDS under
+  // two register budgets; the last two (4 and 5 in single, 2 and 3 in double
+  // precision) = VALU kernel with each point's degrees split over 2 or 4 waves.
+  // Without the image the batched step runs variant 1's kernel for variants 1 to
+  // 3, and the adjoint's accumulation pass variant 0's for variants 0 to 3 (the
+  // split kernels for theirs).
   int field_variants() const override { return sizeof(R) == 4 ? 6 : 4; }
   // the first split variant (two parts; the next one has four)
   static constexpr int kSplitVariant = sizeof(R) == 4 ? 4 : 2;

@@ -460,9 +460,9 @@ void fill_coef_common(CoefArgs<R>& ca, const scf_plan* p) {
 
 // Sum of `rows` partial rows (FP32 or FP64) in double precision, then the
 // coefficients (coef, nullable), the force weights of a history row (W,
-// nullable) and the field weights FW (with the operand image: image).  Up to kSmallRows rows: one pass (a
-// block of 1024 threads per (l, j)); otherwise chunk sums first (two launches,
-// fixed order either way).
+// nullable) and the field weights FW (with the operand image: image).  Up to
+// kSmallRows rows: one pass (a block per (l, j)); otherwise chunk sums first
+// (two launches, fixed order either way).
 constexpr int kSmallRows = 2048;
 
 scf_status reduce_and_finalize(scf_plan* p, const void* partials, int rows, double* coef, void* W,
