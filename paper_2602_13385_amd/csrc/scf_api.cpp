@@ -454,7 +454,7 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
     // opening half kick and drift with the stored accelerations
     {
       Timed t(p, s, K_KICK);
-      HIP_TRY(launch_kick_drift(p->dtype, n, x, y, z, x, y, z, vx, vy, vz, ax, ay, az, h, dt, s));
+      HIP_TRY(launch_kick_drift(p->dtype, n, x, y, z, vx, vy, vz, ax, ay, az, h, dt, s));
     }
     double gc[3];
     centre_accel(hd, R, gc);
@@ -778,7 +778,7 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     if (nsteps == 0) return SCF_OK;
     {
       Timed t(p, s, K_KICK);
-      HIP_TRY(launch_kick_drift(p->dtype, n, x, y, z, x, y, z, vx, vy, vz, ax, ay, az, h, dt, s));
+      HIP_TRY(launch_kick_drift(p->dtype, n, x, y, z, vx, vy, vz, ax, ay, az, h, dt, s));
     }
     // the graph of one middle step (kick dt, drift dt), captured once per
     // distinct argument set on the plan's capture stream
@@ -958,8 +958,10 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
     if (n > 0) {
       // ---- forward recompute of the segment, keeping X_k and W_k --------------
       const void* src[6] = {x0, y0, z0, vx0, vy0, vz0};
-      void* const dst[6] = {Xk(0, 0), Xk(0, 1), Xk(0, 2), Vb[0], Vb[1], Vb[2]};
-      HIP_TRY(launch_copy6(p->dtype, n, src, dst, s));
+      for (int c = 0; c < 3; ++c) {
+        HIP_TRY(hipMemcpyAsync(Xk(0, c), src[c], n * rs, hipMemcpyDeviceToDevice, s));
+        HIP_TRY(hipMemcpyAsync(Vb[c], src[3 + c], n * rs, hipMemcpyDeviceToDevice, s));
+      }
       row_of(0, row);
       if (w_hist) {
         Timed t(p, s, K_MAKE_W);
@@ -973,8 +975,10 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
       st = run_field<Rt>(p, n, Xk(0, 0), Xk(0, 1), Xk(0, 2), Vb[0], Vb[1], Vb[2], Ab[0], Ab[1],
                          Ab[2], nullptr, Wk(0), hp, row, 0, 0.0, 0.0, s);
       if (st != SCF_OK) return st;
-      HIP_TRY(launch_kick_drift(p->dtype, n, Xk(0, 0), Xk(0, 1), Xk(0, 2), Xk(1, 0), Xk(1, 1),
-                                Xk(1, 2), Vb[0], Vb[1], Vb[2], Ab[0], Ab[1], Ab[2], h, dt, s));
+      for (int c = 0; c < 3; ++c)
+        HIP_TRY(hipMemcpyAsync(Xk(1, c), Xk(0, c), n * rs, hipMemcpyDeviceToDevice, s));
+      HIP_TRY(launch_kick_drift(p->dtype, n, Xk(1, 0), Xk(1, 1), Xk(1, 2), Vb[0], Vb[1], Vb[2], Ab[0],
+                                Ab[1], Ab[2], h, dt, s));
       for (int k = 1; k <= nsteps; ++k) {
         if (!w_hist) {
           st = run_coeffs<Rt>(p, n, Xk(k, 0), Xk(k, 1), Xk(k, 2), m, (double*)(w + A.L.coef),

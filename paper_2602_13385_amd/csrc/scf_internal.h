@@ -233,13 +233,8 @@ hipError_t launch_make_w(int dtype, const double* coef, const WeightTables& wt, 
 // field weights of `rows` force-weight rows of a history
 hipError_t launch_expand_w(int dtype, const void* W, int rows, const WeightTables& wt, void* FW,
                            hipStream_t s);
-// six arrays of n values, one launch
-hipError_t launch_copy6(int dtype, int64_t n, const void* const (&src)[6], void* const (&dst)[6],
-                        hipStream_t s);
-// v += kick a; (xo, yo, zo) = (x, y, z) + drift v (xo may be x)
-hipError_t launch_kick_drift(int dtype, int64_t n, const void* x, const void* y, const void* z,
-                             void* xo, void* yo, void* zo, void* vx, void* vy, void* vz,
-                             const void* ax, const void* ay, const void* az, double kick,
+hipError_t launch_kick_drift(int dtype, int64_t n, void* x, void* y, void* z, void* vx, void* vy,
+                             void* vz, const void* ax, const void* ay, const void* az, double kick,
                              double drift, hipStream_t s);
 hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t s);
 // batched mode (cluster-segmented) reduction and finalisation

@@ -215,11 +215,9 @@ __global__ void __launch_bounds__(64) expand_w_kernel(const R* __restrict__ W, W
   emit_row<R>(v, f0, f1, lj, n, wt, FW + k * W_stride);
 }
 
-// v += kick a; (xo, yo, zo) = (x, y, z) + drift v (xo may be x)
 template <typename R>
-__global__ void __launch_bounds__(256) kick_drift_kernel(int64_t n, const R* x, const R* y,
-                                                         const R* z, R* xo, R* yo, R* zo, R* vx,
-                                                         R* vy, R* vz, const R* ax, const R* ay,
+__global__ void __launch_bounds__(256) kick_drift_kernel(int64_t n, R* x, R* y, R* z, R* vx, R* vy,
+                                                         R* vz, const R* ax, const R* ay,
                                                          const R* az, R kick, R drift) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -227,23 +225,9 @@ __global__ void __launch_bounds__(256) kick_drift_kernel(int64_t n, const R* x, 
   vx[i] = u;
   vy[i] = v;
   vz[i] = w;
-  xo[i] = fma(drift, u, x[i]);
-  yo[i] = fma(drift, v, y[i]);
-  zo[i] = fma(drift, w, z[i]);
-}
-
-// Six arrays of n values in one launch, by 4-byte words (array blockIdx.y): the
-// start of an adjoint segment.  Bound by its launch: as six copies it was five
-// more, each with a gap on the stream.  With the first drift writing the next
-// positions itself (three copies fewer), a 20-step gradient at 1e5 particles
-// takes 2406 us against 2521.
-struct Copy6 {
-  const uint32_t* src[6];
-  uint32_t* dst[6];
-};
-__global__ void __launch_bounds__(256) copy6_kernel(Copy6 a, int64_t words) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < words) a.dst[blockIdx.y][i] = a.src[blockIdx.y][i];
+  x[i] = fma(drift, u, x[i]);
+  y[i] = fma(drift, v, y[i]);
+  z[i] = fma(drift, w, z[i]);
 }
 
 // Batched reduction: cluster c owns partial rows [rows[c], rows[c+1]);
@@ -382,35 +366,19 @@ hipError_t launch_expand_w(int dtype, const void* W, int rows, const WeightTable
   return hipGetLastError();
 }
 
-hipError_t launch_copy6(int dtype, int64_t n, const void* const (&src)[6], void* const (&dst)[6],
-                        hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  Copy6 a;
-  for (int c = 0; c < 6; ++c) {
-    a.src[c] = (const uint32_t*)src[c];
-    a.dst[c] = (uint32_t*)dst[c];
-  }
-  const int64_t words = n * (dtype == 0 ? 1 : 2);
-  copy6_kernel<<<dim3((unsigned)((words + 255) / 256), 6), 256, 0, s>>>(a, words);
-  return hipGetLastError();
-}
-
-hipError_t launch_kick_drift(int dtype, int64_t n, const void* x, const void* y, const void* z,
-                             void* xo, void* yo, void* zo, void* vx, void* vy, void* vz,
-                             const void* ax, const void* ay, const void* az, double kick,
+hipError_t launch_kick_drift(int dtype, int64_t n, void* x, void* y, void* z, void* vx, void* vy,
+                             void* vz, const void* ax, const void* ay, const void* az, double kick,
                              double drift, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t grid = (n + 255) / 256;
   if (dtype == 0)
     kick_drift_kernel<float><<<dim3((unsigned)grid), 256, 0, s>>>(
-        n, (const float*)x, (const float*)y, (const float*)z, (float*)xo, (float*)yo, (float*)zo,
-        (float*)vx, (float*)vy, (float*)vz, (const float*)ax, (const float*)ay, (const float*)az,
-        (float)kick, (float)drift);
+        n, (float*)x, (float*)y, (float*)z, (float*)vx, (float*)vy, (float*)vz, (const float*)ax,
+        (const float*)ay, (const float*)az, (float)kick, (float)drift);
   else
     kick_drift_kernel<double><<<dim3((unsigned)grid), 256, 0, s>>>(
-        n, (const double*)x, (const double*)y, (const double*)z, (double*)xo, (double*)yo,
-        (double*)zo, (double*)vx, (double*)vy, (double*)vz, (const double*)ax, (const double*)ay,
-        (const double*)az, kick, drift);
+        n, (double*)x, (double*)y, (double*)z, (double*)vx, (double*)vy, (double*)vz,
+        (const double*)ax, (const double*)ay, (const double*)az, kick, drift);
   return hipGetLastError();
 }
 
