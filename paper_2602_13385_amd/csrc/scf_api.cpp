@@ -165,8 +165,10 @@ scf_status scf_autotune_field(scf_plan* p, int64_t n, const void* x, const void*
   p->prof = false;
   const int saved = p->field_variant;
   scf_status st = p->dtype == SCF_F32
-                      ? run_coeffs<float>(p, n, x, y, z, m, (double*)(w + L.coef), w + L.W, w, L, s)
-                      : run_coeffs<double>(p, n, x, y, z, m, (double*)(w + L.coef), w + L.W, w, L, s);
+                      ? run_coeffs<float>(p, n, x, y, z, m, (double*)(w + L.coef), w + L.W,
+                                          use_image(p, n), w, L, s)
+                      : run_coeffs<double>(p, n, x, y, z, m, (double*)(w + L.coef), w + L.W,
+                                           use_image(p, n), w, L, s);
   if (st != SCF_OK) {
     p->prof = prof;
     return st;
@@ -337,8 +339,8 @@ scf_status scf_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, cons
   hipStream_t s = (hipStream_t)stream;
   char* w = (char*)ws;
   if (p->dtype == SCF_F32)
-    return run_coeffs<float>(p, n, x, y, z, m, coef, w + L.W, w, L, s);
-  return run_coeffs<double>(p, n, x, y, z, m, coef, w + L.W, w, L, s);
+    return run_coeffs<float>(p, n, x, y, z, m, coef, nullptr, false, w, L, s);
+  return run_coeffs<double>(p, n, x, y, z, m, coef, nullptr, false, w, L, s);
 }
 
 scf_status scf_forces(scf_plan* p, int64_t n, const void* x, const void* y, const void* z,
@@ -362,7 +364,8 @@ scf_status scf_forces(scf_plan* p, int64_t n, const void* x, const void* y, cons
   char* w = (char*)ws;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, w + L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), nullptr, w + L.W,
+                          s));
   }
   double cen[6] = {0, 0, 0, 0, 0, 0};
   if (with_host) {
@@ -445,7 +448,7 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
       // a(x0) from the particles themselves
       cen_row(row);
       st = run_coeffs<Rt>(p, n, x, y, z, m, nsteps == 0 && coef_last ? coef_last : coef_int, FW,
-                          w, L, s, Wk(0));
+                          field_image(p, n), w, L, s, Wk(0));
       if (st != SCF_OK) return st;
       st = run_field<Rt>(p, n, x, y, z, vx, vy, vz, ax, ay, az, nullptr, FW, hp, row, 0, 0.0, 0.0, s);
       if (st != SCF_OK) return st;
@@ -463,8 +466,8 @@ scf_status step_impl(scf_plan* p, int64_t n, void* x, void* y, void* z, void* vx
     for (int k = 1; k <= nsteps; ++k) {
       const bool last = k == nsteps;
       cen_row(row);
-      st = run_coeffs<Rt>(p, n, x, y, z, m, last && coef_last ? coef_last : coef_int, FW, w, L, s,
-                          Wk(k));
+      st = run_coeffs<Rt>(p, n, x, y, z, m, last && coef_last ? coef_last : coef_int, FW,
+                          field_image(p, n), w, L, s, Wk(k));
       if (st != SCF_OK) return st;
       // closing half kick of step k merged with the opening half kick of
       // step k+1, then the drift of step k+1
@@ -754,9 +757,8 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
         }
         HIP_TRY(launch_reduce_final_batched(
             p->dtype, !one_pass, part, (const int32_t*)(dev + up.rows), nch,
-            one_pass ? max_cluster_rows : nch, ncl, weight_tables(p, use_image(p, n / ncl)), coef, Wb,
-            W_stride,
-            (const double*)(dev + up.tab), (double*)(w + B.cur), (int*)(dev + up.ctr), q));
+            one_pass ? max_cluster_rows : nch, ncl, weight_tables(p, field_image(p, n / ncl)), coef,
+            Wb, W_stride, (const double*)(dev + up.tab), (double*)(w + B.cur), (int*)(dev + up.ctr), q));
       }
       ForceArgs<Rt> f2 = fa;
       f2.kick = Rt(kick);
@@ -969,7 +971,7 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
                                 weight_tables(p, use_image(p, n)), w + A.Wsv, s));
       } else {
         st = run_coeffs<Rt>(p, n, Xk(0, 0), Xk(0, 1), Xk(0, 2), m, (double*)(w + A.L.coef), Wk(0),
-                            w, A.L, s);
+                            use_image(p, n), w, A.L, s);
         if (st != SCF_OK) return st;
       }
       st = run_field<Rt>(p, n, Xk(0, 0), Xk(0, 1), Xk(0, 2), Vb[0], Vb[1], Vb[2], Ab[0], Ab[1],
@@ -982,7 +984,7 @@ scf_status scf_step_adjoint(scf_plan* p, int64_t n, const void* x0, const void* 
       for (int k = 1; k <= nsteps; ++k) {
         if (!w_hist) {
           st = run_coeffs<Rt>(p, n, Xk(k, 0), Xk(k, 1), Xk(k, 2), m, (double*)(w + A.L.coef),
-                              Wk(k), w, A.L, s);
+                              Wk(k), use_image(p, n), w, A.L, s);
           if (st != SCF_OK) return st;
         }
         if (k == nsteps) break;

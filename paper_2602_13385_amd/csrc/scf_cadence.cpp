@@ -219,7 +219,7 @@ scf_status delta_impl(scf_plan* p, int64_t n, int ns, const void* const* sx, con
   double* ctmp = (double*)(ws + C.ctmp);
   for (int j = 0; j < ns; ++j) {
     const R* sj = base + (int64_t)j * 3 * cap;
-    scf_status st = run_coeffs<R>(p, nc, sj, sj + cap, sj + 2 * cap, dw, ctmp, ws + C.L.W, ws, C.L, s);
+    scf_status st = run_coeffs<R>(p, nc, sj, sj + cap, sj + 2 * cap, dw, ctmp, nullptr, false, ws, C.L, s);
     if (st != SCF_OK) return st;
     HIP_TRY(launch_axpy(p->T, 1.0 / ns, ctmp, coef, s));
   }
@@ -231,14 +231,14 @@ template <typename R>
 scf_status complete_impl(scf_plan* p, int64_t n, int ns, const void* const* sx,
                          const void* const* sy, const void* const* sz, const void* w, double* coef,
                          char* ws, const CadLayout& C, hipStream_t s) {
-  if (ns == 1) return run_coeffs<R>(p, n, sx[0], sy[0], sz[0], w, coef, ws + C.L.W, ws, C.L, s);
+  if (ns == 1) return run_coeffs<R>(p, n, sx[0], sy[0], sz[0], w, coef, nullptr, false, ws, C.L, s);
   {
     Timed t(p, s, K_FILL);
     HIP_TRY(launch_fill(coef, p->T, 0.0, s));
   }
   double* ctmp = (double*)(ws + C.ctmp);
   for (int j = 0; j < ns; ++j) {
-    scf_status st = run_coeffs<R>(p, n, sx[j], sy[j], sz[j], w, ctmp, ws + C.L.W, ws, C.L, s);
+    scf_status st = run_coeffs<R>(p, n, sx[j], sy[j], sz[j], w, ctmp, nullptr, false, ws, C.L, s);
     if (st != SCF_OK) return st;
     HIP_TRY(launch_axpy(p->T, 1.0 / ns, ctmp, coef, s));
   }
@@ -271,7 +271,7 @@ scf_status density_impl(scf_plan* p, int64_t n, const void* x, const void* y, co
   void* W = ws + C.L.W;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), p->d_kden, W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), p->d_kden, W, s));
   }
   HostParams<R> none;
   std::memset(&none, 0, sizeof(none));
@@ -524,7 +524,7 @@ scf_status scf_step_frozen(scf_plan* p, int64_t n, void* x, void* y, void* z, vo
   fill_host_params(hd, with_host ? host : nullptr);
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, w + L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), nullptr, w + L.W, s));
   }
   double R[3] = {centre[0], centre[1], centre[2]}, V[3] = {centre[3], centre[4], centre[5]};
   const bool av = (step_flags & SCF_STEP_ACC_VALID) != 0;
@@ -558,7 +558,7 @@ scf_status scf_select(scf_plan* p, int64_t n, const void* x, const void* y, cons
   char* wsp = (char*)ws;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, wsp + C.L.W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), nullptr, wsp + C.L.W, s));
   }
   const size_t nr = (size_t)n * p->rs;
   char* acc = wsp + C.acc;
@@ -622,7 +622,8 @@ scf_status scf_cadence_init(scf_plan* p, int64_t n, const void* x, const void* y
   auto go = [&](auto tag) -> scf_status {
     using Rt = decltype(tag);
     // coefficients (and force weights) of all particles, then the selection
-    scf_status st = run_coeffs<Rt>(p, n, x, y, z, m, coef, wsp + C.L.W, wsp, C.L, s);
+    scf_status st = run_coeffs<Rt>(p, n, x, y, z, m, coef, wsp + C.L.W, field_image(p, n), wsp,
+                                    C.L, s);
     if (st != SCF_OK) return st;
     st = select_impl<Rt>(p, n, x, y, z, vx, vy, vz, m, wsp + C.L.W, frac, w, nullptr, acc, acc + nr,
                          acc + 2 * nr, state, wsp, C, s);
@@ -673,7 +674,7 @@ scf_status scf_evolve(scf_plan* p, int64_t n, void* x, void* y, void* z, void* v
   void* wnew = wsp + C.wnew;
   {
     Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, W, s));
+    HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), nullptr, W, s));
   }
   auto go = [&](auto tag) -> scf_status {
     using Rt = decltype(tag);
@@ -762,7 +763,7 @@ scf_status scf_evolve(scf_plan* p, int64_t n, void* x, void* y, void* z, void* v
       if (n > 0) HIP_TRY(hipMemcpyAsync(w, wnew, nr, hipMemcpyDeviceToDevice, s));
       {
         Timed t(p, s, K_MAKE_W);
-        HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, true), nullptr, W, s));
+        HIP_TRY(launch_make_w(p->dtype, coef, weight_tables(p, image_variant(p)), nullptr, W, s));
       }
       HIP_TRY(hipStreamSynchronize(s));
       state->nbound = sel.nbound;

@@ -222,7 +222,7 @@ hipError_t launch_reduce(int dtype, const void* partials, int nblocks, int T, in
 // Sums of partial rows [0, nrows) (rows of T = (nmax+1)(lmax+1)^2 values, (l, j)
 // major, n fastest; real = the plan's type, or double chunk sums when
 // chunks_f64), then the coefficients (coef, nullable), the force weights of
-// one row of a weight history (W, nullable) and the field weights FW.
+// one row of a weight history (W, nullable) and the field weights FW (nullable).
 hipError_t launch_reduce_final(int dtype, bool chunks_f64, const void* partials, int nrows,
                                const WeightTables& wt, double* coef, void* W, void* FW,
                                hipStream_t s);

@@ -306,6 +306,12 @@ size_t fw_elems(const scf_plan* p) {
 // nothing and use the image at every n.
 constexpr int64_t kImageRatio = 160;
 bool use_image(const scf_plan* p, int64_t n) { return n >= kImageRatio * p->T; }
+// ... and the plan's field variant is one that reads it (the Hessian-vector pass
+// goes by use_image alone)
+bool image_variant(const scf_plan* p) {
+  return p->rs == 4 && (p->field_variant == 2 || p->field_variant == 3);
+}
+bool field_image(const scf_plan* p, int64_t n) { return image_variant(p) && use_image(p, n); }
 WeightTables weight_tables(const scf_plan* p, bool image) {
   return WeightTables{p->nmax, p->lmax, p->nmaxc, image && p->rs == 4, p->d_cs, p->d_fw,
                       p->d_rtab};
@@ -460,7 +466,7 @@ void fill_coef_common(CoefArgs<R>& ca, const scf_plan* p) {
 
 // Sum of `rows` partial rows (FP32 or FP64) in double precision, then the
 // coefficients (coef, nullable), the force weights of a history row (W,
-// nullable) and the field weights FW (with the operand image: image).  Up to
+// nullable) and the field weights FW (nullable; with the operand image: image).  Up to
 // kSmallRows rows: one pass (a block per (l, j)); otherwise chunk sums first
 // (two launches, fixed order either way).
 constexpr int kSmallRows = 2048;
@@ -486,12 +492,13 @@ scf_status reduce_and_finalize(scf_plan* p, const void* partials, int rows, doub
   return SCF_OK;
 }
 
-// coefficients of n particles into coef (device, nullable) and field weights FW
-// (device); with W non-null also the force weights of a history row
+// coefficients of n particles into coef (device, nullable) and, where the caller
+// reads them, field weights FW (device, nullable; with the operand image: image);
+// with W non-null also the force weights of a history row
 template <typename R>
 scf_status run_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, const void* z,
-                      const void* m, double* coef, void* FW, char* ws, const WsLayout& L,
-                      hipStream_t s, void* W = nullptr) {
+                      const void* m, double* coef, void* FW, bool image, char* ws,
+                      const WsLayout& L, hipStream_t s, void* W = nullptr) {
   int64_t stages;
   const int units = coef_units(p, n, &stages);
   const int rpu = units > 0 ? unit_rows(p, p->coef_variant, (stages + units - 1) / units) : 1;
@@ -503,9 +510,11 @@ scf_status run_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, cons
       Timed t(p, s, K_FILL);
       HIP_TRY(launch_fill(coef, p->T, 0.0, s));
     }
-    Timed t(p, s, K_MAKE_W);
-    HIP_TRY(launch_make_w(p->dtype, coef ? coef : (double*)(ws + L.coef), weight_tables(p, true), nullptr,
-                          FW, s));
+    if (FW) {
+      Timed t(p, s, K_MAKE_W);
+      HIP_TRY(launch_make_w(p->dtype, coef ? coef : (double*)(ws + L.coef),
+                            weight_tables(p, image), nullptr, FW, s));
+    }
     return SCF_OK;
   }
   CoefArgs<R> ca;
@@ -524,7 +533,7 @@ scf_status run_coeffs(scf_plan* p, int64_t n, const void* x, const void* y, cons
     Timed t(p, s, K_COEF);
     HIP_TRY(p->eng->launch_coef(&ca, units, p->coef_variant, s));
   }
-  return reduce_and_finalize(p, ca.partials, nb, coef, W, FW, use_image(p, n), ws, L, s);
+  return reduce_and_finalize(p, ca.partials, nb, coef, W, FW, image, ws, L, s);
 }
 
 // Field pass over n particles.  mode 0: a (and psi) into ax, ay, az (pot);
@@ -777,8 +786,8 @@ scf_status run_gamma(scf_plan* p, int64_t n, const void* x, const void* y, const
     HIP_TRY(p->eng->launch_gamma(&ca, units, s));
   }
   const int rows = units * (ca.one_row ? 1 : p->eng->gamma_rows_per_unit());
-  return reduce_and_finalize(p, ws + L.partials, rows, nullptr, nullptr, Wout, use_image(p, n), ws,
-                             L, s);
+  return reduce_and_finalize(p, ws + L.partials, rows, nullptr, nullptr, Wout, field_image(p, n),
+                             ws, L, s);
 }
 
 bool ptr_ok(const void* q) { return q != nullptr; }

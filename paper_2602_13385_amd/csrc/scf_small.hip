@@ -108,7 +108,8 @@ __device__ __forceinline__ double add_rows(const IN* __restrict__& p, const int6
 // a_t = cs_t * sum and the weights follow without another barrier.  One block
 // per (l, j) rather than per 16 consecutive coefficients, so that it has the
 // neighbours n - 1, n + 1 that the radial weights need.
-// FEW: the batched step's few rows per thread (add_rows).
+// FEW: the batched step's few rows per thread (add_rows).  coef, W and FW are
+// nullable.
 template <int NT, int CW, bool FEW, typename IN, typename R>
 __device__ __forceinline__ void reduce_final_row(const IN* __restrict__ partials, int r0, int r1,
                                                  const WeightTables& wt, double* coef, R* W,
@@ -159,7 +160,7 @@ __device__ __forceinline__ void reduce_final_row(const IN* __restrict__ partials
     wk = R(fw * cv);
   }
   if (W && lane <= wt.nmaxc) W[lj * (wt.nmaxc + 1) + lane] = wk;
-  emit_row<R>(wk, f0, f1, lj, lane, wt, FW);
+  if (FW) emit_row<R>(wk, f0, f1, lj, lane, wt, FW);
 }
 
 // Row (l, j) of a block: blocks are dealt to the 8 XCDs in turn (block b runs
