@@ -595,8 +595,9 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     if (p->h_stage) HIP_TRY(hipHostFree(p->h_stage));
     p->h_stage = nullptr;
     p->h_stage_cap = 0;
-    HIP_TRY(hipHostMalloc((void**)&p->h_stage, stage_bytes, hipHostMallocDefault));
-    p->h_stage_cap = stage_bytes;
+    const size_t cap_bytes = staging_capacity(stage_bytes, B.up_bytes);
+    HIP_TRY(hipHostMalloc((void**)&p->h_stage, cap_bytes, hipHostMallocDefault));
+    p->h_stage_cap = cap_bytes;
   }
   if (!p->ev_staging) HIP_TRY(hipEventCreateWithFlags(&p->ev_staging, hipEventDisableTiming));
   char* hs_ = p->h_stage;

@@ -371,9 +371,18 @@ struct BatchUpload {
   }
 };
 
+// Bytes of pinned staging to allocate for a call that needs `need` (its upload
+// and its whole centre table): a re-allocation costs 0.4 ms, so the first one
+// takes what any call on as many particles and clusters needs for up to
+// kCentreRows centre rows (`bound`, where that is at most 1 MiB more), and a
+// longer run's leaves room for half as much again.
+size_t staging_capacity(size_t need, size_t bound) {
+  return need <= bound ? std::min(bound, need + (size_t(1) << 20)) : need + need / 2;
+}
+
 struct BatchLayout {
   WsLayout L;
-  size_t cur, up, total;
+  size_t cur, up, up_bytes, total;
   int max_units;
   int64_t max_blocks;
 };
@@ -393,7 +402,8 @@ BatchLayout batch_layout(const scf_plan* p, int64_t n, int ncl) {
   B.cur = off;
   off += align256((size_t)ncl * 9 * sizeof(double));
   B.up = off;
-  off += BatchUpload(max_units, ncl, B.max_blocks, kCentreRows).total;
+  B.up_bytes = BatchUpload(max_units, ncl, B.max_blocks, kCentreRows).total;
+  off += B.up_bytes;
   B.total = off;
   return B;
 }
