@@ -295,6 +295,10 @@ scf_status scf_plan_create(scf_plan** out, const scf_basis* basis, int32_t dtype
 void scf_plan_destroy(scf_plan* p) {
   if (!p) return;
   for (hipEvent_t e : p->ev_pool) (void)hipEventDestroy(e);
+  if (p->ev_batch) {
+    (void)batch_wait(p);
+    (void)hipEventDestroy(p->ev_batch);
+  }
   if (p->ev_staging) {
     (void)hipEventSynchronize(p->ev_staging);
     (void)hipEventDestroy(p->ev_staging);
@@ -587,6 +591,10 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
 
   // ---- staging (pinned): the upload with the whole centre table at its end ----
   const size_t stage_bytes = up.tab + (size_t)nrows * ncl * 9 * sizeof(double);
+  if (p->batch_stream != s) {
+    const scf_status bs = batch_wait(p);
+    if (bs != SCF_OK) return bs;
+  }
   if (p->staging_pending) {
     HIP_TRY(hipEventSynchronize(p->ev_staging));
     p->staging_pending = false;
@@ -600,6 +608,7 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
     p->h_stage_cap = cap_bytes;
   }
   if (!p->ev_staging) HIP_TRY(hipEventCreateWithFlags(&p->ev_staging, hipEventDisableTiming));
+  if (!p->ev_batch) HIP_TRY(hipEventCreateWithFlags(&p->ev_batch, hipEventDisableTiming));
   char* hs_ = p->h_stage;
   *(int*)(hs_ + up.ctr) = 0;
   {
@@ -803,6 +812,9 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
       add(&p->field_variant, sizeof(p->field_variant));
       add(&coef_int, sizeof(coef_int));
       if (!p->gexec || key != p->gkey) {
+        // (the last call may still be replaying the graphs)
+        const scf_status bs = batch_wait(p);
+        if (bs != SCF_OK) return bs;
         if (p->gexec) HIP_TRY(hipGraphExecDestroy(p->gexec));
         if (p->graph) HIP_TRY(hipGraphDestroy(p->graph));
         if (p->gexec_g) HIP_TRY(hipGraphExecDestroy(p->gexec_g));
@@ -874,6 +886,10 @@ scf_status scf_step_batched(scf_plan* p, int32_t nclusters, const int64_t* offse
   };
   scf_status st = p->dtype == SCF_F32 ? go(float(0)) : go(double(0));
   if (st != SCF_OK && !p->staging_pending) (void)staged();
+  const hipError_t be = hipEventRecord(p->ev_batch, s);
+  p->batch_stream = s;
+  p->batch_pending = be == hipSuccess;
+  if (st == SCF_OK) HIP_TRY(be);
   if (st == SCF_OK) std::copy(cnew.begin(), cnew.end(), centres);
   return st;
 }

@@ -223,6 +223,10 @@ struct scf_plan {
   size_t h_stage_cap = 0;
   hipEvent_t ev_staging = nullptr;
   bool staging_pending = false;
+  // the stream of the last batched call, and its end (batch_wait)
+  hipStream_t batch_stream = nullptr;
+  hipEvent_t ev_batch = nullptr;
+  bool batch_pending = false;
 };
 
 namespace {
@@ -370,6 +374,17 @@ struct BatchUpload {
     total = off;
   }
 };
+
+// Waits on the host until the last batched call's kernels are done.  Its staging
+// is free earlier (ev_staging); this is for what must not happen beside it: a
+// call on another stream (the workspace is usually the same one), and the end of
+// a graph that it may still be replaying.
+scf_status batch_wait(scf_plan* p) {
+  if (!p->batch_pending) return SCF_OK;
+  HIP_TRY(hipEventSynchronize(p->ev_batch));
+  p->batch_pending = false;
+  return SCF_OK;
+}
 
 // Bytes of pinned staging to allocate for a call that needs `need` (its upload
 // and its whole centre table): a re-allocation costs 0.4 ms, so the first one
