@@ -366,10 +366,11 @@ class Plan:
 
     def workspace(self, n, nclusters=1, device=None):
         torch = _torch()
+        n, nclusters = int(n), int(nclusters)  # (compared by value, not by identity)
         key, size = self._need
         if key != (n, nclusters):
             need = C.c_size_t()
-            _check(lib().scf_workspace_size(self._h, int(n), int(nclusters), C.byref(need)))
+            _check(lib().scf_workspace_size(self._h, n, nclusters, C.byref(need)))
             size = need.value
             self._need = ((n, nclusters), size)
         if self._ws is None or self._ws.numel() < size:
