@@ -175,10 +175,12 @@ scf_status scf_step_keep_weights(scf_plan* plan, int64_t n, void* x, void* y, vo
  * and frame centre (centres: host, nclusters*6 = R, V per cluster, in/out,
  * advanced in double precision on the host); all share the host potential.
  * One step is one launch each of the coefficient, reduction, finalisation and
- * field kernels for all clusters together, driven by static work lists (a
+ * field kernels for all clusters together, driven by work lists (a
  * cluster's particle ranges per wave-unit, its partial rows, its 256-particle
- * field blocks) built on the host per call.  The kernels are launched
- * directly on stream by default.  With SCF_STEP_GRAPH (and without
+ * field blocks) built on the host per call and uploaded in one copy with the
+ * first centre rows, from pinned staging that the plan keeps: the host may
+ * return, and the next call on the same stream start, while the kernels run.
+ * The kernels are launched directly on stream by default.  With SCF_STEP_GRAPH (and without
  * SCF_STEP_NO_GRAPH) the middle steps (all but the last) are instead
  * replayed from HIP graphs of one and of eight steps, captured once on a
  * plan-owned stream and recaptured when pointers, sizes, dt or the host
@@ -188,7 +190,9 @@ scf_status scf_step_keep_weights(scf_plan* plan, int64_t n, void* x, void* y, vo
  * scf_workspace_size(plan, n, nclusters).  step_flags and the returned state
  * are as for scf_step; coef_last (device, nullable) receives nclusters*ncoef
  * doubles, cluster-major.  A plan must not run two batched calls
- * concurrently (the graph and the pinned staging buffers are per plan). */
+ * concurrently (the graph and the pinned staging buffers are per plan): two
+ * host threads must not be in the call together.  A call on another stream than
+ * the plan's last batched call waits on the host until that one is done. */
 scf_status scf_step_batched(scf_plan* plan, int32_t nclusters, const int64_t* offsets, void* x,
                             void* y, void* z, void* vx, void* vy, void* vz, const void* m,
                             void* ax, void* ay, void* az, uint32_t step_flags, const scf_host* host,
@@ -470,22 +474,32 @@ scf_status scf_autotune(scf_plan* plan, int64_t n, const void* x, const void* y,
  * radial sums of Eq. total_potential on the vector ALUs, under two register
  * budgets per thread (the compiler's own, or one that allows at least 4 waves
  * per SIMD); their results are bitwise identical.  Single-precision plans add
- * variants 2 and 3: the same sums as 4x4x1 matrix-core (MFMA) products in
- * persistent blocks, again under two register budgets (the compiler's own, or
- * 5 waves per SIMD); these two agree bitwise with each other and, since they
- * sum in another order, with variants 0 and 1 to the single-precision force
- * tolerance.  The last two variants (4 and 5 in single, 2 and 3 in double
+ * variants 2 and 3: the same sums as 4x4x1 matrix-core (MFMA) products.  In
+ * scf_forces and scf_density at every n, and in steps (plain, batched, frozen,
+ * adjoint) and the selection of at least 160 particles per basis term (n >= 160
+ * ncoef; in a batch the mean n of its clusters), both are one kernel that reads
+ * the products' operands from global memory, where the reduction wrote them.  In
+ * steps of fewer particles they are persistent blocks that build the operands in
+ * LDS, under two register budgets (the compiler's own, or 5 waves per SIMD).
+ * Either way the two agree bitwise with each other and, since each kernel sums in
+ * an order of its own, with variants 0 and 1 (and a run across the 160 ncoef with
+ * one below it) to the single-precision force tolerance.  The last two variants (4 and 5 in single, 2 and 3 in double
  * precision) run the vector-ALU sums with each particle's degrees split over
  * 2 or 4 waves of one block, which add their partial sums through LDS: more
  * waves for few particles; they agree with variants 0 and 1 to the force
- * tolerance of the plan's precision.  The batched step runs variant 1's
- * kernel for every variant above 0 (its per-cluster blocks measured faster
- * on the vector ALUs), and the adjoint's accumulation pass runs variant 0's
- * for variants 0 to 3 and the split kernels for theirs.  scf_autotune_field
- * computes the coefficients of the given particles, times each variant on
- * the forces at those particles (written to ax, ay, az, device, caller-owned;
- * synchronising the stream) and keeps the fastest for the plan; best_ms
- * (nullable) receives its time. */
+ * tolerance of the plan's precision.  Where variants 2 and 3 build their
+ * operands in LDS (fewer than 160 particles per term), the batched step runs
+ * variant 1's kernel and the adjoint's accumulation pass variant 0's in their
+ * place; the split variants run as variant 1 in the batched step and as
+ * themselves in the accumulation pass.  The adjoint's Hessian-vector pass does
+ * not go by the variant: in single precision it runs on the matrix cores from 160
+ * particles per term on, else on the vector ALUs.  scf_autotune_field computes
+ * the coefficients of the given particles, times the kernels that a step of that
+ * many particles runs (of variants 2 and 3, where they are one kernel, variant 3
+ * alone) on the forces at those particles (written to ax, ay, az, device,
+ * caller-owned; synchronising the stream) and keeps the fastest for the plan;
+ * best_ms (nullable) receives its time.  A plan used on other sizes, or on
+ * batches of small clusters, keeps that choice. */
 int32_t scf_plan_num_field_variants(const scf_plan* plan);
 int32_t scf_plan_field_variant(const scf_plan* plan);
 scf_status scf_plan_set_field_variant(scf_plan* plan, int32_t variant);

@@ -111,7 +111,7 @@ struct ForceArgs {
   const R* beta_rad;  // as in CoefArgs
   const R* beta_ang;
   const R* beta_img;  // monic Gegenbauer recurrence to degree NMAXC + 1, [(lmax+1)][NMAXC+2]
-  int image;          // the matrix-core variants read the operand image (kImageRatio)
+  int image;          // the matrix-core variants read the operand image (use_image)
   int64_t n;
   R binv, alpha, inv_alpha;
   int amode;

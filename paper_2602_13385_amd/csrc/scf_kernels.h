@@ -1127,7 +1127,9 @@ field_mfma_kernel_o5(ForceArgs<float> a) {
 // fresh image, so all its lines are requested first (touch_lines).  Measured
 // against the kernel above (us per step-mode launch after a reduction): 102
 // and 117 at 1e6 points, nmax 16, lmax 10; 7.4 and 10.2 at 1e5, nmax 10, lmax
-// 6; batched (against the vector kernel, which that path ran) see kImageRatio.
+// 6; batched (against the vector kernel, which that path runs otherwise), eight
+// clusters of 160 T: 267 and 339 at nmax 16, lmax 10, 31.6 and 36.0 at nmax 10,
+// lmax 6.
 // (The FP32 MFMAs run on the vector ALUs' own multipliers, here and in a
 // microbenchmark of separate waves, so the time is about the sum of the two.)
 
@@ -1431,9 +1433,10 @@ field_image_kernel(ForceArgs<float> a) {
 // With the weights fixed, a particle's substeps do not depend on the other
 // particles, so one launch takes up to kRunEvals of them with the state in
 // registers: no launch, no kernel tail and no load of the weights into cold
-// caches per substep (interval of 159 substeps, 1e5 particles, nmax 10, lmax 6:
-// see the launch sequence, frozen_steps).  Same arithmetic as the one-substep
-// kernels, variant by variant.
+// caches per substep: an interval of 159 substeps at 1e5 particles, nmax 10,
+// lmax 6, with its selection and refresh, takes 1047 us, and took 1438 with a
+// launch per substep.  Same arithmetic as the one-substep kernels, variant by
+// variant.
 template <typename R>
 struct RunState {
   R x, y, z, vx, vy, vz, ax, ay, az;

@@ -300,14 +300,24 @@ constexpr int kReduceChunks = 32;
 size_t fw_elems(const scf_plan* p) {
   return (size_t)FwLayout::elems(p->nmaxc, p->lmax, p->rs == 4);
 }
-// Whether the matrix-core variants read the operand image (the faster kernel
-// at every size) in a run of clusters of n particles.  The two kernels sum in
-// different orders, and a run amplifies the last bits of its forces: after ten
-// steps of 0.01 the coefficients differ by about 1e-8 sqrt(T / n) (measured 4 to
-// 14e-10 at n = 130 T over five basis sizes, Plummer and Hernquist).  Clusters
-// of fewer than kImageRatio T particles keep the kernels, and the bits, that
-// their runs have had.  Single evaluations (scf_forces, the density) amplify
-// nothing and use the image at every n.
+// Whether the matrix-core variants read the operand image in a run of one
+// cluster of n particles, or of several of n on average.  The line is one of
+// reproducibility, not of speed or accuracy: the image kernel is the faster one
+// and no less exact at every n (us per step-mode launch at 10, 40 and 160 T
+// points, image / the best of the others: nmax 6, lmax 4 3.8/4.9, 3.9/4.9,
+// 4.1/5.1; nmax 10, lmax 6 5.6/6.5, 5.7/6.7, 7.9/9.5; nmax 16, lmax 10
+// 11.6/12.3, 16.4/20.2, 40.6/48.7; force error against 64 bits 0.83e-7 and
+// 0.91e-7 rms at 10 T of the first, 0.80e-7 and 1.00e-7 at 160 T of the last).
+// But it sums in another order, and a run carries that into its coefficients:
+// after ten steps of 0.01 they differ by about 1e-8 sqrt(T / n) (measured 4 to
+// 14e-10 at n = 130 T over five basis sizes, Plummer and Hernquist).  From 160 T
+// on that stays below 1e-9; runs of fewer particles keep their former kernels.
+// A batch goes by its mean size, since a launch runs one kernel: with both in
+// one, chosen per cluster, ten clusters of 1.2e6 particles, 18% of them in
+// clusters below the line, took 589 us instead of 541 (585 with the vector kernel
+// for all).  So a small cluster beside large ones is evaluated from the image.
+// Single evaluations (scf_forces, the density) carry nothing on and use the
+// image at every n.
 constexpr int64_t kImageRatio = 160;
 bool use_image(const scf_plan* p, int64_t n) { return n >= kImageRatio * p->T; }
 // ... and the plan's field variant is one that reads it (the Hessian-vector pass
